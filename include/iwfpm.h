@@ -81,11 +81,13 @@ enum { IWFPM_PRECOND_NONE = 0, IWFPM_PRECOND_PLAIN = 1, IWFPM_PRECOND_LEARNED = 
 typedef struct {
     int precision;       /* IWFPM_PREC_*: arithmetic of the potential convolution.
                             FP32 keeps the kinetic term, the boundary vectors and
-                            everything in the eigensolver in float64. */
+                            everything in the eigensolver in float64.  (The few-mode
+                            convolution is float64 either way, see iwfpm_plan.) */
     int window_variant;  /* IWFPM_WINDOW_* */
     int order;           /* IWFPM_ORDER_* */
     int device;          /* HIP device ordinal; -1 = host-only plan (geometry queries only) */
-    int schedule;        /* IWFPM_SCHED_*; AUTO picks FUSED when the grid fits one workgroup */
+    int schedule;        /* IWFPM_SCHED_*; AUTO picks FUSED when the grid fits one workgroup,
+                            and the few-mode convolution for potentials it suits */
     int split;           /* THREEPASS: number of leading grid axes in the middle pass; 0 = auto */
     int tile;            /* THREEPASS: middle-pass tile width (columns); 0 = auto */
 } iwfpm_opts;
@@ -105,7 +107,12 @@ const char* iwfpm_status_string(int status);
  * potential, trailing axes with the kinetic term), else, when the leading
  * block fits no workgroup either (e.g. 40^3 x 10^3), five: a further pass
  * transforms the axes between the two groups before and after the middle
- * one.  Host inputs (P, K, L, modes, vhat) are copied; the caller may free
+ * one.  With IWFPM_SCHED_AUTO and no split or tile named, a potential of few
+ * modes (one pair +-m per axis, or up to 4 to 16 pairs in all, by the number of
+ * k_I axes and the precision) is applied without transforms, as the
+ * wrapped convolution sum_m Vhat_m psi[(k* - m) mod ext] that F V F^{-1}
+ * equals, in float64 and without a workspace; a named schedule always runs
+ * the transforms.  Host inputs (P, K, L, modes, vhat) are copied; the caller may free
  * them on return.  opts may be NULL (defaults).  Blocking.
  * Errors: ERR_ARG (d < 1, n <= d, n > 8, K/L < 1, non-finite P or vhat),
  * ERR_UNSUPPORTED (a grid extent 2K_j or 2L_j the library has no transform
@@ -238,7 +245,10 @@ int iwfpm_batch_destroy(iwfpm_batch_t batch);
  * extents) are reused and new ones appended (one line per key).  best_us
  * (may be NULL) receives the best time per apply in microseconds, or -1 when
  * the cache answered.  Allocates 2 x nvec vectors of scratch; blocking.
- * iwfpm_schedule - the current schedule for `precision`: out[5] = {fused,
+ * A plan that takes the few-mode convolution at that precision has nothing to
+ * choose: it is timed alone and no cache is read or written.
+ * iwfpm_schedule - the current transform schedule for `precision` (also where
+ * the few-mode convolution is taken instead): out[5] = {fused,
  * split, tile, slabs per workgroup, threads of the middle pass's workgroups
  * (of the fused kernel's when fused)}.
  * Errors: ERR_ARG, ERR_NODEVICE, ERR_UNSUPPORTED, ERR_ALLOC, ERR_DEVICE.
@@ -252,7 +262,7 @@ int iwfpm_schedule(iwfpm_plan_t plan, int precision, int32_t* out);
  * apply's own stream before and after each kernel (fused, or passes 1-3);
  * nothing blocks while recording.  Enabling resets the totals.
  * iwfpm_profile_read - totals since the last enable: ms[4] summed kernel time
- * (fused, pass 1, pass 2, pass 3), launches[4], points[4] (grid points x
+ * (fused or few-mode convolution, pass 1, pass 2, pass 3), launches[4], points[4] (grid points x
  * vectors processed).  Synchronises with the outstanding events.
  * Errors: ERR_ARG, ERR_NODEVICE, ERR_DEVICE.
  */

@@ -34,14 +34,29 @@ struct iwfpm_batch_s {
     size_t lds = 0;
     int grid = 0;
     bool use_graph = false;
+    bool transforms = false;              // some plan takes the transform passes
+    std::vector<FewLaunch> few;           // few-mode plans: one launch per kind of kernel
+    size_t few_off = 0, start_off = 0;    // table offsets: B FewItems, then B + 1 starts per launch
     hipGraphExec_t gexec = nullptr;
     hipStream_t gstream = nullptr;
 };
 
 static size_t items_offset() { return (sizeof(BatchHead) + 255) / 256 * 256; }
 
+static hipError_t launch_few(iwfpm_batch_s* b, hipStream_t st) {
+    const unsigned char* table = (const unsigned char*)b->d_table.ptr;
+    for (size_t k = 0; k < b->few.size(); ++k) {
+        const int* start = reinterpret_cast<const int*>(table + b->start_off) + k * (b->B + 1);
+        hipError_t e = launch_few_batch(b->few[k], reinterpret_cast<const FewItem*>(table + b->few_off), start, b->B, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <typename R>
 static hipError_t launch_passes(iwfpm_batch_s* b, hipStream_t st) {
+    if (hipError_t e = launch_few(b, st); e != hipSuccess) return e;
+    if (!b->transforms) return hipSuccess;
     const void* head = b->d_table.ptr;
     const void* items = (const unsigned char*)b->d_table.ptr + items_offset();
     for (int pass = 0; pass < 3; ++pass) {
@@ -86,6 +101,7 @@ int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_
         const Schedule& sc = p->sched[prec];
         if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
         if (!sc.fused && sc.pd.split_mid > 0) return IWFPM_ERR_UNSUPPORTED;  // five-pass grids: apply one by one
+        if (p->few_modes[prec]) continue;
         for (int ax = 0; ax < p->n; ++ax) maxe = std::max(maxe, axis_class(p->geom, ax));
         if (sc.fused) lds = std::max(lds, lds_fused(p->geom, esz));
         else lds = std::max({lds, lds_slabs(p->geom, sc.pd, esz), lds_columns(p->geom, sc.pd, esz)});
@@ -101,13 +117,33 @@ int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_
     b->maxs = extent_class_of(maxe);
     b->lds = lds;
     b->use_graph = use_graph != 0;
-    b->table_bytes = items_offset() + (size_t)B * sizeof(BatchItem);
+    std::vector<FewItem> items(B);
+    for (int i = 0; i < B; ++i) {
+        const iwfpm_plan_s* p = plans[i];
+        items[i].kind = -1;
+        if (!p->few_modes[prec]) {
+            b->transforms = true;
+            continue;
+        }
+        items[i].g = p->geom;
+        items[i].sd = p->stencil;
+        items[i].w = p->star;
+        const int kind = items[i].kind = few_kind(p->geom, p->stencil, p->star);
+        bool known = false;
+        for (const FewLaunch& l : b->few) known = known || l.kind == kind;
+        if (!known) b->few.push_back(FewLaunch{kind, 0, 0, 0});
+    }
+    b->few_off = (items_offset() + (size_t)B * sizeof(BatchItem) + 255) / 256 * 256;
+    b->start_off = (b->few_off + (size_t)B * sizeof(FewItem) + 255) / 256 * 256;
+    b->table_bytes = b->start_off + b->few.size() * (B + 1) * sizeof(int);
     int rc = dev_alloc(b->d_table, b->table_bytes);
     if (rc == IWFPM_OK && hipHostMalloc((void**)&b->h_table, b->table_bytes) != hipSuccess) rc = IWFPM_ERR_ALLOC;
     if (rc == IWFPM_OK && hipEventCreateWithFlags(&b->staged, hipEventDisableTiming) != hipSuccess)
         rc = IWFPM_ERR_DEVICE;
     int per_cu = 0, cus = 0;
-    if (rc == IWFPM_OK) {
+    for (FewLaunch& l : b->few)
+        if (rc == IWFPM_OK && few_launch_config(l, items.data(), B) != hipSuccess) rc = IWFPM_ERR_DEVICE;
+    if (rc == IWFPM_OK && b->transforms) {
         hipError_t e = prec ? occupancy<float>(b->maxs, lds, &per_cu) : occupancy<double>(b->maxs, lds, &per_cu);
         if (e != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             rc = IWFPM_ERR_DEVICE;
@@ -138,8 +174,26 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
     BatchHead* head = reinterpret_cast<BatchHead*>(b->h_table);
     BatchItem* items = reinterpret_cast<BatchItem*>(b->h_table + items_offset());
     int tot[3] = {0, 0, 0};
+    FewItem* few = reinterpret_cast<FewItem*>(b->h_table + b->few_off);
+    int* start = reinterpret_cast<int*>(b->h_table + b->start_off);
+    double few_points = 0.0;
+    for (int i = 0; i < b->B; ++i)
+        if (b->plans[i]->few_modes[b->prec]) few_points += (double)b->plans[i]->geom.N * nvec[i];
     for (int i = 0; i < b->B; ++i) {
         iwfpm_plan_s* p = b->plans[i];
+        few[i].kind = -1;
+        if (p->few_modes[b->prec]) {
+            FewItem& f = few[i];
+            std::memset(&f, 0, sizeof(f));
+            f.g = p->geom;
+            f.t = p->tabs;
+            f.sd = p->stencil;
+            f.w = p->star;
+            f.psi = reinterpret_cast<const double2*>(psi[i]);
+            f.hpsi = reinterpret_cast<double2*>(hpsi[i]);
+            f.nvec = nvec[i];
+            f.kind = few_kind(f.g, f.sd, f.w);
+        }
         const Schedule& sc = p->sched[b->prec];
         BatchItem& it = items[i];
         std::memset(&it, 0, sizeof(it));
@@ -153,7 +207,9 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
         it.fused = sc.fused ? 1 : 0;
         for (int k = 0; k < 3; ++k) it.start[k] = tot[k];
         const int nv = nvec[i];
-        if (sc.fused) {
+        if (few[i].kind >= 0) {
+            // no workgroups here: see below
+        } else if (sc.fused) {
             tot[0] += nv;
         } else {
             const int bpv = (sc.pd.s_out + sc.pd.slabs_per_wg - 1) / sc.pd.slabs_per_wg;
@@ -162,6 +218,11 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
             tot[1] += ntile * nv;
             tot[2] += bpv * nv;
         }
+    }
+    for (size_t k = 0; k < b->few.size(); ++k) {
+        int* s = start + k * (b->B + 1);
+        s[0] = 0;
+        for (int i = 0; i < b->B; ++i) s[i + 1] = s[i] + (few[i].kind == b->few[k].kind ? few_blocks(few[i], few_points) : 0);
     }
     head->B = b->B;
     for (int k = 0; k < 3; ++k) head->total[k] = tot[k];

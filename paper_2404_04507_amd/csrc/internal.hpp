@@ -34,6 +34,7 @@ struct DevGeom {
 // Device pointers owned by the plan.
 struct DevTabs {
     const int* slice_a;       // per k_II slice: lower window end a_j = -K_j - floor(q_j), nslice x d
+    const int* slice_m;       // slice_a modulo the axis' extent
     const double* slice_g;    // per k_II slice: 2 pi (P_II k_II)_j, nslice x d
     const float* vtab32;      // per-axis potential tables (already divided by N)
     const double* vtab64;

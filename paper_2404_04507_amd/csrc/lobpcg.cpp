@@ -1980,6 +1980,8 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
         if (!b.p->sched[b.prec].ok) b.prec = 1 - b.prec;
         if (!b.p->sched[b.prec].ok) return IWFPM_ERR_UNSUPPORTED;
         b.can64 = b.p->sched[0].ok;
+        // few-mode applies are float64 in either precision: nothing to switch
+        if (b.can64 && b.p->few_modes[0] && b.p->few_modes[1]) b.prec = 0;
         b.hnorm = b.p->lam_max + b.p->vsum_abs;
         b.floor32 = 30.0 * 6e-8 * b.p->vsum_abs / b.hnorm;
         b.eta.assign(m, 1.0);
@@ -2191,7 +2193,7 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
         for (int i : iter) {
             BInst& b = in[i];
             ++b.it;
-            if (b.prec == 0 && b.p->opts.precision == 1) ++b.polished;
+            if (b.prec == 0 && b.p->opts.precision == 1 && !b.p->few_modes[1]) ++b.polished;
             // active set: the pairs not yet converged (soft locking)
             b.act.clear();
             for (int j = 0; j < m; ++j)
@@ -2540,6 +2542,7 @@ int iwfpm_destroy(iwfpm_plan_t p) {
         DeviceGuard g(p->opts.device);
         (void)hipDeviceSynchronize();
         dev_free(p->d_slice_a);
+        dev_free(p->d_slice_m);
         dev_free(p->d_slice_g);
         dev_free(p->d_vtab32);
         dev_free(p->d_vtab64);

@@ -287,6 +287,8 @@ static int build_geometry(iwfpm_plan_s* p) {
     return IWFPM_OK;
 }
 
+static void build_stencil(iwfpm_plan_s* p);
+
 static int build_potential(iwfpm_plan_s* p, int n_modes, const int32_t* modes, const double* vhat) {
     const int n = p->n, d = p->d;
     // merge duplicate modes
@@ -323,6 +325,7 @@ static int build_potential(iwfpm_plan_s* p, int n_modes, const int32_t* modes, c
         p->vim.push_back(im);
     }
     const int nm = (int)p->vre.size();
+    build_stencil(p);
     const DevGeom& g = p->geom;
     bool axis_aligned = true;
     for (int i = 0; i < nm && axis_aligned; ++i) {
@@ -361,6 +364,9 @@ static int build_potential(iwfpm_plan_s* p, int n_modes, const int32_t* modes, c
         p->vgrid.clear();
     } else {
         p->geom.vmode = 1;
+        p->vtab.clear();
+        p->vgrid.clear();
+        if (p->few_modes[0] && p->few_modes[1]) return IWFPM_OK;  // only the transforms read it
         p->vgrid.assign(g.N, 0.0);
         std::vector<int> l(n);
         for (long long gp = 0; gp < g.N; ++gp) {
@@ -383,9 +389,133 @@ static int build_potential(iwfpm_plan_s* p, int n_modes, const int32_t* modes, c
             }
             p->vgrid[gp] = v * invN;
         }
-        p->vtab.clear();
     }
     return IWFPM_OK;
+}
+
+// A star of neighbours (one pair on each axis, as a lattice of cosines has)
+// takes the walk along axis 0; its pairs are then in axis order.
+static void build_star(iwfpm_plan_s* p) {
+    const DevGeom& g = p->geom;
+    StencilDesc& sd = p->stencil;
+    const int n = p->n, d = p->d;
+    StarDesc& w = p->star;
+    w = StarDesc{};
+    if (!star_supported(n, d)) return;
+    // pair j on axis j alone
+    StencilDesc s2 = sd;
+    for (int j = 0; j < kStencilMaxPairs; ++j) {
+        s2.cr[j] = s2.ci[j] = 0.0;
+        for (int ax = 0; ax < n; ++ax) s2.off[j][ax] = 0;
+    }
+    bool used[kMaxAxes] = {};
+    for (int m = 0; m < sd.np; ++m) {
+        int ax = -1, nz = 0;
+        for (int a = 0; a < n; ++a)
+            if (sd.off[m][a]) {
+                ax = a;
+                ++nz;
+            }
+        if (sd.cr[m] == 0.0 && sd.ci[m] == 0.0) continue;  // padding
+        if (nz != 1 || used[ax]) return;
+        used[ax] = true;
+        s2.cr[ax] = sd.cr[m];
+        s2.ci[ax] = sd.ci[m];
+        s2.off[ax][ax] = sd.off[m][ax];
+    }
+    // the axes whose neighbours are a thread's own points: steps of one
+    for (int ax = 0; ax < std::min(2, n - d); ++ax) {
+        if (!used[ax]) continue;
+        if (g.ext[ax] > 2 && s2.off[ax][ax] == g.ext[ax] - 1) {  // -1: the pair the other way round
+            s2.off[ax][ax] = 1;
+            s2.ci[ax] = -s2.ci[ax];
+        }
+        if (s2.off[ax][ax] != 1) return;
+    }
+    w.plane = g.stride[n - std::min(d, 2) - 1];
+    // a workgroup holds whole planes; positions within a step are 32-bit byte
+    // offsets; and planes of few points would leave most lanes idle (n <= 4:
+    // one plane is all there is of a slice)
+    if (w.plane > (n == 6 ? 512 : 1024) || g.stride[0] >= (1 << 28)) return;
+    if (n < 6 && 2 * w.plane < (w.plane + 63) / 64 * 64) return;
+    s2.np = n;
+    sd = s2;
+    w.ok = 1;
+}
+
+// Few-mode potentials take the wrapped convolution instead of transforms.
+// Its cost grows with the pairs of modes while the transforms' does not; the
+// lines lie where the convolution's lead is still sure on every grid of the
+// kind (us, convolution against transforms, graph replays on one card):
+//   float64, d <= 2: 12 pairs 211 : 335 (24^2 x 32^2, 16 vectors), 23 : 43
+//     (16^2 x 20^2, 6 vectors); 16 pairs 367 : 336 and 37 : 43
+//   float32, d <= 2: 8 pairs 131 : 164 and 18 : 28; 12 pairs 211 : 165 and 23 : 28
+//   d = 1: 16 pairs 17.5 : 69 (float64), : 61 (float32) on 1024 x 42, 8 vectors
+//   float64, d = 3: 4 pairs 90 : 153 (10^6, 5 vectors), 8 pairs 176 : 153
+//   float32, d = 3: 4 pairs 90 : 109, 8 pairs 176 : 109
+// A star is cheaper still and always takes it (16^6, 6 pairs, 3 vectors: 497
+// against 1,733 and 1,082).
+static int stencil_max_pairs(int d, int prec) {
+    if (d == 1) return 16;
+    if (d == 2) return prec ? 8 : 12;
+    return prec ? 4 : 6;
+}
+
+static void build_stencil(iwfpm_plan_s* p) {
+    const DevGeom& g = p->geom;
+    const int n = p->n, d = p->d;
+    p->few_modes[0] = p->few_modes[1] = false;
+    // a schedule, split or tile that the caller names is a transform schedule
+    if (p->opts.schedule != IWFPM_SCHED_AUTO || p->opts.split > 0 || p->opts.tile > 0) return;
+    if (d > kStencilMaxD) return;
+    StencilDesc& sd = p->stencil;
+    sd = StencilDesc{};
+    sd.real = 1;
+    int np = 0;
+    const int nm = (int)p->vre.size();
+    for (int i = 0; i < nm; ++i) {
+        const int* m = &p->modes[(size_t)i * n];
+        int lead = 0;
+        for (int j = 0; j < n && lead == 0; ++j) lead = m[j];
+        if (lead == 0) sd.c0 = p->vre[i];
+        if (lead <= 0) continue;
+        // the partner -m (build_potential checked that it is there); V is
+        // the real part of the modes' sum, so the pair takes the mean of the
+        // two coefficients that should be conjugate
+        double re = p->vre[i], im = p->vim[i];
+        for (int k = 0; k < nm; ++k) {
+            bool neg = true;
+            for (int j = 0; j < n && neg; ++j) neg = p->modes[(size_t)k * n + j] == -m[j];
+            if (!neg) continue;
+            re = 0.5 * (re + p->vre[k]);
+            im = 0.5 * (im - p->vim[k]);
+            break;
+        }
+        if (re == 0.0 && im == 0.0) continue;
+        if (np == kStencilMaxPairs) return;
+        sd.cr[np] = re;
+        sd.ci[np] = im;
+        if (im != 0.0) sd.real = 0;
+        for (int j = 0; j < n; ++j) {
+            const int ax = axis_of(d, n, j), E = g.ext[ax];
+            sd.off[np][ax] = (short)(((m[j] % E) + E) % E);
+        }
+        ++np;
+    }
+#define IWFPM_CASE(c) if (sd.np == 0 && c >= np) sd.np = c;
+    IWFPM_STENCIL_PAIRS(IWFPM_CASE)
+#undef IWFPM_CASE
+    for (int ax = 0; ax < n; ++ax) {
+        if (g.ext[ax] > 32767) return;  // offsets are 16-bit
+        sd.dext[ax] = fast_div((unsigned)g.ext[ax]);
+    }
+    sd.dslice = fast_div((unsigned)g.nkI);
+    sd.ns_max = stencil_slices(g, kStencilThreads);
+    if (stencil_lds(g, sd) > 32 * 1024) return;
+    sd.tile_row = std::max(1, g.stride[0] / kStencilThreads / 8);
+    build_star(p);
+    for (int prec = 0; prec < 2; ++prec)
+        p->few_modes[prec] = p->star.ok || np <= stencil_max_pairs(d, prec);
 }
 
 static const size_t kLdsDefault = 64 * 1024;
@@ -684,6 +814,7 @@ static int prepare_kernels() {
     e = prepare_batch<R, 16>(b); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
     e = prepare_batch<R, 32>(b); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
     e = prepare_batch<R, 64>(b); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
+    e = prepare_stencil(); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
     return IWFPM_OK;
 }
 
@@ -701,6 +832,12 @@ static int upload_tables(iwfpm_plan_s* p) {
     int rc;
     if ((rc = upload(p->d_slice_a, p->slice_a)) != IWFPM_OK) return rc;
     if ((rc = upload(p->d_slice_g, p->slice_g)) != IWFPM_OK) return rc;
+    std::vector<int> am(p->slice_a.size());
+    for (size_t e = 0; e < am.size(); ++e) {
+        const int E = p->geom.ext[p->n - p->d + (int)(e % p->d)];
+        am[e] = ((p->slice_a[e] % E) + E) % E;
+    }
+    if ((rc = upload(p->d_slice_m, am)) != IWFPM_OK) return rc;
     std::vector<float> f32;
     if (!p->vtab.empty()) {
         if ((rc = upload(p->d_vtab64, p->vtab)) != IWFPM_OK) return rc;
@@ -720,6 +857,7 @@ static int upload_tables(iwfpm_plan_s* p) {
     p->tabs.tw32 = (const float*)p->d_tw32.ptr;
     p->tabs.tw64 = (const double*)p->d_tw64.ptr;
     p->tabs.slice_a = (const int*)p->d_slice_a.ptr;
+    p->tabs.slice_m = (const int*)p->d_slice_m.ptr;
     p->tabs.slice_g = (const double*)p->d_slice_g.ptr;
     p->tabs.vtab32 = (const float*)p->d_vtab32.ptr;
     p->tabs.vtab64 = (const double*)p->d_vtab64.ptr;
@@ -816,7 +954,7 @@ static const size_t kWorkspaceCap = (size_t)4 << 30;
 int plan_ensure_ws(iwfpm_plan_s* p, int nvec, int prec, hipStream_t st) {
     const Schedule& sc = p->sched[prec];
     if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
-    if (sc.fused) return IWFPM_OK;
+    if (sc.fused || p->few_modes[prec]) return IWFPM_OK;
     size_t need = (size_t)p->geom.N * (prec ? 8 : 16) * nvec;
     if (p->d_ws.bytes < need) {
         if (hipStreamSynchronize(st) != hipSuccess) return IWFPM_ERR_DEVICE;
@@ -831,6 +969,15 @@ int plan_apply_ws(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int pr
     const int prec = precision == IWFPM_PREC_FP32 ? 1 : 0;
     const Schedule& sc = p->sched[prec];
     if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
+    if (p->few_modes[prec]) {
+        // float64 throughout at the same cost as float32, and no workspace
+        DevGeom g = p->geom;
+        g.kin = kinetic ? 1 : 0;
+        hipEvent_t* ev = prof_slot(kinetic ? &p->prof : nullptr, true, (long long)nvec * g.N, st);
+        const hipError_t e = launch_stencil(g, p->tabs, p->stencil, p->star, psi, hpsi, nvec, st);
+        if (ev) (void)hipEventRecord(ev[1], st);
+        return e == hipSuccess ? IWFPM_OK : IWFPM_ERR_DEVICE;
+    }
     const size_t esz = prec ? 8 : 16;
     const long long N = p->geom.N;
     int chunk = nvec;
@@ -859,7 +1006,7 @@ int plan_apply(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int preci
     const int prec = precision == IWFPM_PREC_FP32 ? 1 : 0;
     const Schedule& sc = p->sched[prec];
     if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
-    if (!sc.fused) {
+    if (!sc.fused && !p->few_modes[prec]) {
         // the plan's own workspace, grown to the vectors of one chunk
         const size_t per = (size_t)p->geom.N * (prec ? 8 : 16);
         const int chunk = (int)std::max<size_t>(1, std::min<size_t>((size_t)nvec, kWorkspaceCap / per));
@@ -1144,14 +1291,17 @@ int iwfpm_tune(iwfpm_plan_t p, int nvec, int precision, void* stream, double* be
     hipStream_t st = (hipStream_t)stream;
     std::vector<Schedule> cands = schedule_candidates(p, prec);
     if (cands.empty()) return IWFPM_ERR_UNSUPPORTED;
-    if (cands.size() == 1 && !cands[0].fused && cands[0].pd.split_mid > 0) {
+    // the few-mode convolution has no schedule to choose: it is timed alone
+    const bool few = p->few_modes[prec];
+    if (few) cands.assign(1, p->sched[prec]);
+    if (!few && cands.size() == 1 && !cands[0].fused && cands[0].pd.split_mid > 0) {
         p->sched[prec] = cands[0];  // the one five-pass schedule: nothing to choose
         if (best_us) *best_us = -1.0;
         return IWFPM_OK;
     }
     const std::string key = tune_key(p, prec, nvec);
     const char* cache = std::getenv("IWFPM_TUNE_CACHE");
-    if (cache && cache[0]) {
+    if (!few && cache && cache[0]) {
         Schedule sc{};
         if (tune_cache_lookup(cache, key, sc, p, prec)) {
             if (sc.fused) {
@@ -1210,7 +1360,7 @@ int iwfpm_tune(iwfpm_plan_t p, int nvec, int precision, void* stream, double* be
     }
     p->sched[prec] = best_sc;
     if (best_us) *best_us = best;
-    if (cache && cache[0]) {
+    if (!few && cache && cache[0]) {
         if (FILE* f = std::fopen(cache, "a")) {
             std::fprintf(f, "%s %d %d %d %d %.3f %d\n", key.c_str(), best_sc.fused ? 1 : 0, best_sc.pd.split,
                          best_sc.pd.tile, best_sc.pd.slabs_per_wg, best, best_sc.pd.threads_outer);

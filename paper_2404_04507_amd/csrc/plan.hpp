@@ -9,6 +9,7 @@
 
 #include "../../include/iwfpm.h"
 #include "internal.hpp"
+#include "stencil.hpp"
 
 namespace iwfpm {
 
@@ -67,11 +68,15 @@ struct iwfpm_plan_s {
     double vsum_nonzero = 0.0;    // sum over m != 0 of |Vhat_m|
     double vsum_abs = 0.0;        // sum over all m of |Vhat_m|
     double lam_max = 0.0;
+    // few-mode potentials: the apply as a wrapped convolution (stencil.hpp)
+    bool few_modes[2] = {false, false};  // by precision, as sched
+    iwfpm::StencilDesc stencil{};
+    iwfpm::StarDesc star{};
     // schedules per precision: [0] float64, [1] float32
     iwfpm::Schedule sched[2];
     // device
     bool host_only = true;
-    iwfpm::DeviceBuf d_slice_a, d_slice_g, d_vtab32, d_vtab64, d_vgrid32, d_vgrid64, d_tw32, d_tw64;
+    iwfpm::DeviceBuf d_slice_a, d_slice_m, d_slice_g, d_vtab32, d_vtab64, d_vgrid32, d_vgrid64, d_tw32, d_tw64;
     iwfpm::DeviceBuf d_ws;        // apply workspace
     iwfpm::DeviceBuf d_ef_freq;   // eigenfunction output: (P k)_j per window point (d x N)
     iwfpm::DeviceBuf d_ef_ws;     // eigenfunction output: per-axis tables and slice partials
