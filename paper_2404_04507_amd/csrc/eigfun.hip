@@ -17,6 +17,18 @@
 // products per complex one), split over the window points into slices whose
 // partial grids are summed in a fixed order, so results do not depend on the
 // launch shape's timing.
+//
+// When P_I is diagonal, (P k)_j depends on k_j and on the k_II slice alone, so
+// the sum over the last k_I axis separates:
+//
+//     T[(s, r)][c] = sum_p U[s, r, p] E_{d-1}[(s, p)][c],
+//     u[m][c]      = sum_(s, r) A[(s, r)][m] T[(s, r)][c],
+//
+// s the slice, p the position along the last k_I axis, r those along the
+// others: the dense contraction runs over N / 2K_d rows instead of N points
+// (and its tables and their sines shrink alike).  The paper's 2D grid (1001 x
+// 1001) for N = 5,760 takes 107 us instead of 1,033: the
+// contraction 96 (40 TFLOP/s), the rows 8, the reduction of two slices 8.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -192,6 +204,65 @@ __global__ void k_ef_zero(long long total, double2* __restrict__ out) {
         out[e] = make_double2(0.0, 0.0);
 }
 
+// T[(s, r)][c] of slices [s0, s0 + gridDim.y): a workgroup takes one slice and
+// 64 columns; the slice's exponentials of kEfRow positions at a time go to LDS
+// and each wave sums four rows per LDS read (the four products of a read
+// cover its LDS time), U at wave-uniform addresses.
+constexpr int kEfRow = 32;
+__global__ void __launch_bounds__(256) k_ef_rows(const double* __restrict__ f, const double2* __restrict__ U, int s0,
+                                                 int Rs, int El, int nc, double o, double h,
+                                                 double2* __restrict__ T) {
+    __shared__ double2 E[kEfRow][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = blockIdx.x * 64 + lane;
+    const int sl = blockIdx.y;
+    const long long s = s0 + sl;
+    const double xi = o + h * (double)c;
+    for (int r0 = 0; r0 < Rs; r0 += 16) {
+        const int r = r0 + 4 * wave;
+        double2 acc[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = make_double2(0.0, 0.0);
+        for (int p0 = 0; p0 < El; p0 += kEfRow) {
+            const int np = min(kEfRow, El - p0);
+            if (r0 == 0 || El > kEfRow) {  // the exponentials of a short axis stay for all rows
+                __syncthreads();
+                for (int q = wave; q < np; q += 4) {
+                    double t = f[s * El + p0 + q] * xi;
+                    t -= rint(t);
+                    double sn, cs;
+                    sincospi(2.0 * t, &sn, &cs);
+                    E[q][lane] = make_double2(cs, sn);
+                }
+                __syncthreads();
+            }
+            const double2* u = U + (s * Rs + r) * El + p0;
+            if (r + 4 <= Rs) {
+                for (int q = 0; q < np; ++q) {
+                    const double2 e = E[q][lane];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const double2 a = u[(long long)v * El + q];
+                        acc[v].x += a.x * e.x - a.y * e.y;
+                        acc[v].y += a.x * e.y + a.y * e.x;
+                    }
+                }
+            } else {
+                for (int v = 0; v < 4; ++v)
+                    if (r + v < Rs)
+                        for (int q = 0; q < np; ++q) {
+                            const double2 e = E[q][lane], a = u[(long long)v * El + q];
+                            acc[v].x += a.x * e.x - a.y * e.y;
+                            acc[v].y += a.x * e.y + a.y * e.x;
+                        }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (r + v < Rs && c < nc) T[((long long)sl * Rs + r + v) * nc + c] = acc[v];
+    }
+}
+
 constexpr size_t kEfTableBudget = (size_t)256 << 20;    // bytes of per-axis tables per chunk
 constexpr size_t kEfPartialBudget = (size_t)512 << 20;  // bytes of slice partials
 
@@ -210,6 +281,49 @@ int ensure_freq(iwfpm_plan_s* p, hipStream_t st) {
             double acc = 0.0;
             for (int l = 0; l < p->n; ++l) acc += p->P[(size_t)j * p->n + l] * (double)k[l];
             f[(size_t)j * N + vp] = acc;
+        }
+    }
+    dev_free(p->d_ef_freq);
+    if (int rc = dev_alloc(p->d_ef_freq, bytes)) return rc;
+    if (hipMemcpyAsync(p->d_ef_freq.ptr, f.data(), bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return IWFPM_ERR_DEVICE;
+    return IWFPM_OK;
+}
+
+// P_I diagonal: the sum over the last k_I axis separates
+bool separable(const iwfpm_plan_s* p) {
+    for (int j = 0; j < p->d; ++j)
+        for (int l = 0; l < p->d; ++l)
+            if (j != l && p->P[(size_t)j * p->n + l] != 0.0) return false;
+    return true;
+}
+
+// the same for a separable plan: (P k)_j of every row (s, r), j < d - 1, then
+// (P k)_{d-1} of every (s, p)
+int ensure_row_freq(iwfpm_plan_s* p, hipStream_t st) {
+    const DevGeom& g = p->geom;
+    const int d = p->d, El = g.ext[p->n - 1], Rs = g.nkI / El;
+    const size_t rows = (size_t)p->nslice * Rs, tail = (size_t)p->nslice * El;
+    const size_t bytes = (rows * (d - 1) + tail) * sizeof(double);
+    if (p->d_ef_freq.ptr && p->d_ef_freq.bytes >= bytes) return IWFPM_OK;
+    std::vector<double> f(rows * (d - 1) + tail);
+    std::vector<int> k(p->n);
+    auto freq = [&](int j) {
+        double acc = 0.0;
+        for (int l = 0; l < p->n; ++l) acc += p->P[(size_t)j * p->n + l] * (double)k[l];
+        return acc;
+    };
+    for (long long s = 0; s < p->nslice; ++s) {
+        const long long first = s * g.nkI;
+        for (int r = 0; r < Rs; ++r) {  // grid position of the row's first point, and the row it is in vector order
+            host_label(p, first + (long long)r * El, k.data());
+            const size_t row = (size_t)(host_grid_to_vec(p, first + (long long)r * El) / El);
+            for (int j = 0; j + 1 < d; ++j) f[(size_t)j * rows + row] = freq(j);
+        }
+        for (int q = 0; q < El; ++q) {
+            host_label(p, first + q, k.data());
+            f[rows * (d - 1) + (size_t)s * El + (size_t)(host_grid_to_vec(p, first + q) % El)] = freq(d - 1);
         }
     }
     dev_free(p->d_ef_freq);
@@ -242,8 +356,11 @@ extern "C" int iwfpm_eigenfunction(iwfpm_plan_t p, const void* u, const double* 
     DeviceGuard guard(p->opts.device);
     if (!guard.ok) return IWFPM_ERR_DEVICE;
     hipStream_t st = (hipStream_t)stream;
-    const long long N = p->geom.N;
-    if (int rc = ensure_freq(p, st)) return rc;
+    // contraction rows: window points, or rows of the last k_I axis
+    const bool sep = separable(p);
+    const int El = p->geom.ext[p->n - 1], Rs = p->geom.nkI / El;
+    const long long N = sep ? p->geom.N / El : p->geom.N;
+    if (int rc = sep ? ensure_row_freq(p, st) : ensure_freq(p, st)) return rc;
 
     EfGemm g{};
     g.d = d;
@@ -263,10 +380,14 @@ extern "C" int iwfpm_eigenfunction(iwfpm_plan_t p, const void* u, const double* 
     long long np = (long long)(kEfTableBudget / (sizeof(double2) * (size_t)row));
     np = std::max(4LL, np - np % 4);
     np = std::min(np, ((N + 3) / 4) * 4);
+    if (sep) np = std::max<long long>(1, std::min<long long>(np, 32768LL * Rs) / Rs) * Rs;  // whole slices
     // slices: enough workgroups for the chip, at least 64 window points each,
     // partials within their budget (one slice writes the output directly)
-    long long S = std::max(1LL, std::min((2048 + tiles - 1) / tiles, 64LL));
+    // (two per CU: more slices only add partial grids, 16 MB each on 1001 x
+    // 1001; without them a row contraction of 480 rows has no time to hide them)
+    long long S = std::max(1LL, std::min(((sep ? 512 : 2048) + tiles - 1) / tiles, 64LL));
     S = std::min(S, std::max(1LL, np / 64));
+    if (sep && d == 1) S = 1;  // no contraction after the rows' own
     S = std::min(S, std::max(1LL, (long long)(kEfPartialBudget / (sizeof(double2) * (size_t)total))));
     const size_t tab_bytes = sizeof(double2) * (size_t)np * (size_t)row;
     const size_t part_bytes = S > 1 ? sizeof(double2) * (size_t)S * (size_t)total : 0;
@@ -292,13 +413,23 @@ extern "C" int iwfpm_eigenfunction(iwfpm_plan_t p, const void* u, const double* 
         long long off = 0;
         for (int j = 0; j + 1 < d; ++j) {
             g.aoff[j] = off;
-            k_ef_table<<<grid_blocks(cnt * g.na[j]), 256, 0, st>>>(f + (size_t)j * N, j == 0 ? g.U : nullptr, p0, cnt,
-                                                                 g.na[j], origin[j], step[j], tab + off);
+            k_ef_table<<<grid_blocks(cnt * g.na[j]), 256, 0, st>>>(f + (size_t)j * N, j == 0 && !sep ? g.U : nullptr,
+                                                                 p0, cnt, g.na[j], origin[j], step[j], tab + off);
             off += cnt * g.na[j];
         }
         g.boff = off;
-        k_ef_table<<<grid_blocks(cnt * g.nc), 256, 0, st>>>(f + (size_t)(d - 1) * N, nullptr, p0, cnt, g.nc,
-                                                          origin[d - 1], step[d - 1], tab + off);
+        if (sep) {
+            k_ef_rows<<<dim3((unsigned)g.tiles_c, (unsigned)(cnt / Rs)), 256, 0, st>>>(
+                f + (size_t)(d - 1) * N, g.U, (int)(p0 / Rs), Rs, El, g.nc, origin[d - 1], step[d - 1], tab + off);
+            if (d == 1) {  // the rows are the slices: their sum is the answer
+                k_ef_reduce<<<grid_blocks(total), 256, 0, st>>>(tab + off, (int)cnt, total, p0 > 0, o);
+                if (hipGetLastError() != hipSuccess) return IWFPM_ERR_DEVICE;
+                continue;
+            }
+        } else {
+            k_ef_table<<<grid_blocks(cnt * g.nc), 256, 0, st>>>(f + (size_t)(d - 1) * N, nullptr, p0, cnt, g.nc,
+                                                              origin[d - 1], step[d - 1], tab + off);
+        }
         long long Sc = std::min(S, std::max(1LL, cnt / 64));
         g.ps = (((cnt + Sc - 1) / Sc) + 3) / 4 * 4;
         Sc = (cnt + g.ps - 1) / g.ps;
