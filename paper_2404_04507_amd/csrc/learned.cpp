@@ -56,7 +56,8 @@ struct LearnedPrecond {
     DeviceBuf bwd;    // two S x H scratch arrays, dO as float (S x 2)
     DeviceBuf red;    // dO (S x 2 double), dbeta (3), flag
     DeviceBuf work;   // wblocks blocks of wcols columns
-    DeviceBuf small, partial;  // Gram results / coefficients, Gram partial sums (training)
+    DeviceBuf small, partial;  // coefficients of combinations, Gram partial sums (training)
+    double2* h_small = nullptr;  // pinned: Gram results (the reduction writes them here), then kCoefSlots coefficient slots
     int wcols = 0, wblocks = 0;
     long long version = 0;
 };
@@ -107,6 +108,8 @@ static void lp_release(LearnedPrecond* lp) {
     dev_free(lp->work);
     dev_free(lp->small);
     dev_free(lp->partial);
+    if (lp->h_small) (void)hipHostFree(lp->h_small);
+    lp->h_small = nullptr;
     lp->wcols = lp->wblocks = 0;
 }
 
@@ -273,25 +276,56 @@ static ColPtrs contiguous_cols(const double2* base, int m, long long N) {
 
 using cvec = std::vector<std::complex<double>>;
 
-// out (p x q, column-major) = L^H R
+constexpr int kCoefSlots = 3;
+constexpr size_t kGramOut = (size_t)kMaxCols * kMaxCols, kCoef = (size_t)kMaxCols * kMaxCols / 2;
+
+// out (p x q, column-major) = L^H R: the reduction writes the pinned mirror
 static int dgram(LearnedPrecond* lp, const ColPtrs& L, int p, const ColPtrs& R, int q, cvec& out, hipStream_t st) {
-    double2* dC = (double2*)lp->small.ptr;
-    if (gram(L, p, R, q, lp->N, (double2*)lp->partial.ptr, kGramBlocks, dC, st) != hipSuccess) return IWFPM_ERR_DEVICE;
-    out.assign((size_t)p * q, 0.0);
-    if (hipMemcpyAsync(out.data(), dC, out.size() * sizeof(double2), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if (gram(L, p, R, q, lp->N, (double2*)lp->partial.ptr, kGramBlocks, lp->h_small, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return IWFPM_ERR_DEVICE;
+    out.resize((size_t)p * q);
+    for (size_t e = 0; e < out.size(); ++e) out[e] = {lp->h_small[e].x, lp->h_small[e].y};
     return IWFPM_OK;
 }
 
-// Y_j = beta Y_j + sum_i A_i C[i + j p]
-static int dlincomb(LearnedPrecond* lp, const ColPtrs& A, int p, const ColPtrs& Y, int q, const cvec& C, double beta,
-                    hipStream_t st) {
-    double2* dC = (double2*)lp->small.ptr + kMaxCols * kMaxCols;
-    if (hipMemcpyAsync(dC, C.data(), (size_t)p * q * sizeof(double2), hipMemcpyHostToDevice, st) != hipSuccess ||
-        lincomb(A, p, Y, q, dC, beta, lp->N, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
-        return IWFPM_ERR_DEVICE;
+// A = L^H R and B = L^H L, in one Gram where their columns fit one
+static int dgram2(LearnedPrecond* lp, const ColPtrs& L, const ColPtrs& R, int k, cvec& A, cvec& B, hipStream_t st) {
+    int rc;
+    if (2 * k > kMaxCols) {
+        if ((rc = dgram(lp, L, k, R, k, A, st))) return rc;
+        return dgram(lp, L, k, L, k, B, st);
+    }
+    ColPtrs RL{};
+    for (int j = 0; j < k; ++j) {
+        RL.p[j] = R.p[j];
+        RL.p[k + j] = L.p[j];
+    }
+    cvec AB;
+    if ((rc = dgram(lp, L, k, RL, 2 * k, AB, st))) return rc;
+    A.assign(AB.begin(), AB.begin() + (size_t)k * k);
+    B.assign(AB.begin() + (size_t)k * k, AB.end());
     return IWFPM_OK;
+}
+
+// coefficients into device slot `slot` (its pinned slot is free again: every
+// caller has synchronised the stream in a Gram since it was last used)
+static int dcoef(LearnedPrecond* lp, int slot, const cvec& C, hipStream_t st) {
+    double2* h = lp->h_small + kGramOut + slot * kCoef;
+    if (C.size() > kCoef) return IWFPM_ERR_ARG;
+    for (size_t e = 0; e < C.size(); ++e) h[e] = make_double2(C[e].real(), C[e].imag());
+    return hipMemcpyAsync((double2*)lp->small.ptr + slot * kCoef, h, C.size() * sizeof(double2), hipMemcpyHostToDevice,
+                          st) == hipSuccess
+               ? IWFPM_OK
+               : IWFPM_ERR_DEVICE;
+}
+
+// Y_j = beta Y_j + sum_i A_i C[i + j p], C in device slot `slot`
+static int dlincomb(LearnedPrecond* lp, const ColPtrs& A, int p, const ColPtrs& Y, int q, int slot, double beta,
+                    hipStream_t st) {
+    return lincomb(A, p, Y, q, (double2*)lp->small.ptr + slot * kCoef, beta, lp->N, st) == hipSuccess
+               ? IWFPM_OK
+               : IWFPM_ERR_DEVICE;
 }
 
 static void hermitize(cvec& A, int k) {
@@ -365,14 +399,12 @@ static int lp_backprop(LearnedPrecond* lp, const double2* G, const double2* R, c
     for (int l = kLayers - 1; l >= 0; --l) {
         const float* X = l == 0 ? (const float*)lp->feat.ptr : act_at(lp, 2 * (l - 1) + 1);
         float* dX = l == 0 ? nullptr : (dcur == s0 ? s1 : s0);
-        if (lp_dense_bwd(X, dcur, wbf + n->offw[l], dX, g + n->offw[l], g + n->offb[l], S, n->in[l], n->out[l], st) !=
-            hipSuccess)
+        // dZ_{l-1} = dY_{l-1} .* GELU'(Z_{l-1})
+        const float* Zin = l == 0 ? nullptr : act_at(lp, 2 * (l - 1));
+        if (lp_dense_bwd(X, dcur, wbf + n->offw[l], Zin, dX, g + n->offw[l], g + n->offb[l], S, n->in[l], n->out[l],
+                         st) != hipSuccess)
             return IWFPM_ERR_DEVICE;
-        if (l > 0) {
-            // dZ_{l-1} = dY_{l-1} .* GELU'(Z_{l-1}), in place
-            if (lp_act_bwd(dX, act_at(lp, 2 * (l - 1)), dX, S * kHid, 1, st) != hipSuccess) return IWFPM_ERR_DEVICE;
-            dcur = dX;
-        }
+        if (l > 0) dcur = dX;
     }
     return IWFPM_OK;
 }
@@ -394,8 +426,12 @@ static int lp_rr_loss_grad(LearnedPrecond* lp, const double2* X, int m, const do
     if (m < 1 || 2 * m > kMaxCols) return IWFPM_ERR_ARG;
     int rc = lp_ensure_work(lp, m, WB_COUNT);
     if (rc) return rc;
-    if (!lp->small.ptr && dev_alloc(lp->small, (size_t)2 * kMaxCols * kMaxCols * sizeof(double2)))
+    if (!lp->small.ptr && dev_alloc(lp->small, kCoefSlots * kCoef * sizeof(double2))) return IWFPM_ERR_ALLOC;
+    if (!lp->h_small &&
+        hipHostMalloc((void**)&lp->h_small, (kGramOut + kCoefSlots * kCoef) * sizeof(double2)) != hipSuccess) {
+        lp->h_small = nullptr;
         return IWFPM_ERR_ALLOC;
+    }
     if (!lp->partial.ptr && dev_alloc(lp->partial, (size_t)kGramBlocks * kMaxCols * kMaxCols * sizeof(double2)))
         return IWFPM_ERR_ALLOC;
     iwfpm_plan_s* p = lp->plan;
@@ -409,7 +445,7 @@ static int lp_rr_loss_grad(LearnedPrecond* lp, const double2* X, int m, const do
             Gc = contiguous_cols(G, m, N);
     if ((rc = plan_apply(p, X, HX, m, hprec, st, 1))) return rc;
     cvec Am, Bm, C;
-    if ((rc = dgram(lp, Xc, m, HXc, m, Am, st)) || (rc = dgram(lp, Xc, m, Xc, m, Bm, st))) return rc;
+    if ((rc = dgram2(lp, Xc, HXc, m, Am, Bm, st))) return rc;
     hermitize(Am, m);
     std::vector<double> th;
     if (small_rr(Am, Bm, m, th, C) < m) return IWFPM_OK;  // dependent block: no sample
@@ -417,7 +453,9 @@ static int lp_rr_loss_grad(LearnedPrecond* lp, const double2* X, int m, const do
     for (int j = 0; j < m; ++j) D += th[j] - lam[j];
     const double hn = p->lam_max + p->vsum_abs;
     if (!(D > 1e-12 * m * hn)) return IWFPM_OK;  // already converged: no sample
-    if ((rc = dlincomb(lp, Xc, m, Yc, m, C, 0.0, st)) || (rc = dlincomb(lp, HXc, m, HYc, m, C, 0.0, st))) return rc;
+    if ((rc = dcoef(lp, 0, C, st)) || (rc = dlincomb(lp, Xc, m, Yc, m, 0, 0.0, st)) ||
+        (rc = dlincomb(lp, HXc, m, HYc, m, 0, 0.0, st)))
+        return rc;
     Reals t{};
     for (int j = 0; j < m; ++j) t.v[j] = th[j];
     if (residual(HYc, Yc, Rc, t, m, N, st) != hipSuccess) return IWFPM_ERR_DEVICE;
@@ -432,7 +470,7 @@ static int lp_rr_loss_grad(LearnedPrecond* lp, const double2* X, int m, const do
         HS.p[m + j] = HW + (size_t)j * N;
     }
     cvec A2, B2, C2;
-    if ((rc = dgram(lp, S, k, HS, k, A2, st)) || (rc = dgram(lp, S, k, S, k, B2, st))) return rc;
+    if ((rc = dgram2(lp, S, HS, k, A2, B2, st))) return rc;
     hermitize(A2, k);
     std::vector<double> th2;
     const int r2 = small_rr(A2, B2, k, th2, C2);
@@ -454,7 +492,9 @@ static int lp_rr_loss_grad(LearnedPrecond* lp, const double2* X, int m, const do
                 P2[i + (size_t)l * k] -= v * th2[j];
             }
         }
-    if ((rc = dlincomb(lp, HS, k, Gc, m, P1, 0.0, st)) || (rc = dlincomb(lp, S, k, Gc, m, P2, 1.0, st))) return rc;
+    if ((rc = dcoef(lp, 1, P1, st)) || (rc = dcoef(lp, 2, P2, st)) ||
+        (rc = dlincomb(lp, HS, k, Gc, m, 1, 0.0, st)) || (rc = dlincomb(lp, S, k, Gc, m, 2, 1.0, st)))
+        return rc;
     return lp_backprop(lp, G, R, A, Cc, m, st);
 }
 

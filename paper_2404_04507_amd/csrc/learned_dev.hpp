@@ -15,11 +15,10 @@ namespace iwfpm {
 // Y[s][o] = act(sum_i X[s][i] W[i][o] + b[o]) for s < S; Z (optional) keeps the pre-activation
 hipError_t lp_dense_fwd(const float* X, const uint16_t* W, const float* b, float* Z, float* Y, int S, int in, int out,
                         int act, hipStream_t st);
-// dZ = dY .* act'(Z)
-hipError_t lp_act_bwd(const float* dY, const float* Z, float* dZ, int n, int act, hipStream_t st);
-// dX = dZ W^T (skipped when dX is null), dW = X^T dZ, db = column sums of dZ
-hipError_t lp_dense_bwd(const float* X, const float* dZ, const uint16_t* W, float* dX, float* dW, float* db, int S,
-                        int in, int out, hipStream_t st);
+// dX = (dZ W^T) .* GELU'(Zin), Zin the pre-activations of the layer below (skipped when dX is null),
+// dW = X^T dZ, db = column sums of dZ
+hipError_t lp_dense_bwd(const float* X, const float* dZ, const uint16_t* W, const float* Zin, float* dX, float* dW,
+                        float* db, int S, int in, int out, hipStream_t st);
 // Adam on float32 master weights w (moments m, v) with bias corrections c1, c2;
 // refreshes the bfloat16 copy wbf
 hipError_t lp_adam(float* w, float* m, float* v, const float* g, uint16_t* wbf, int n, float lr, float b1, float b2,
