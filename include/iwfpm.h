@@ -112,7 +112,7 @@ const char* iwfpm_status_string(int status);
  * k_I axes and the precision) is applied without transforms, as the
  * wrapped convolution sum_m Vhat_m psi[(k* - m) mod ext] that F V F^{-1}
  * equals, in float64 and without a workspace; a named schedule always runs
- * the transforms.  Host inputs (P, K, L, modes, vhat) are copied; the caller may free
+ * the transforms, and so do the eigensolvers.  Host inputs (P, K, L, modes, vhat) are copied; the caller may free
  * them on return.  opts may be NULL (defaults).  Blocking.
  * Errors: ERR_ARG (d < 1, n <= d, n > 8, K/L < 1, non-finite P or vhat),
  * ERR_UNSUPPORTED (a grid extent 2K_j or 2L_j the library has no transform
@@ -245,8 +245,8 @@ int iwfpm_batch_destroy(iwfpm_batch_t batch);
  * extents) are reused and new ones appended (one line per key).  best_us
  * (may be NULL) receives the best time per apply in microseconds, or -1 when
  * the cache answered.  Allocates 2 x nvec vectors of scratch; blocking.
- * A plan that takes the few-mode convolution at that precision has nothing to
- * choose: it is timed alone and no cache is read or written.
+ * Where the plan's applies take the few-mode convolution, this is the schedule
+ * of its solves.
  * iwfpm_schedule - the current transform schedule for `precision` (also where
  * the few-mode convolution is taken instead): out[5] = {fused,
  * split, tile, slabs per workgroup, threads of the middle pass's workgroups

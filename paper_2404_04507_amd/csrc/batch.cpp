@@ -34,11 +34,13 @@ struct iwfpm_batch_s {
     size_t lds = 0;
     int grid = 0;
     bool use_graph = false;
+    bool all_transforms = false;          // no plan takes the few-mode route
     bool transforms = false;              // some plan takes the transform passes
     std::vector<FewLaunch> few;           // few-mode plans: one launch per kind of kernel
     size_t few_off = 0, start_off = 0;    // table offsets: B FewItems, then B + 1 starts per launch
     hipGraphExec_t gexec = nullptr;
     hipStream_t gstream = nullptr;
+    bool few_of(const iwfpm_plan_s* p) const { return !all_transforms && p->few_modes[prec]; }
 };
 
 static size_t items_offset() { return (sizeof(BatchHead) + 255) / 256 * 256; }
@@ -80,9 +82,8 @@ static hipError_t occupancy(int maxs, size_t lds, int* n) {
     }
 }
 
-extern "C" {
-
-int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_graph, iwfpm_batch_t* out) {
+int iwfpm::batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_graph, bool transforms,
+                        iwfpm_batch_t* out) {
     if (!out || B < 1 || !plans) return IWFPM_ERR_ARG;
     *out = nullptr;
     if (precision != IWFPM_PREC_FP64 && precision != IWFPM_PREC_FP32) return IWFPM_ERR_ARG;
@@ -101,7 +102,7 @@ int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_
         const Schedule& sc = p->sched[prec];
         if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
         if (!sc.fused && sc.pd.split_mid > 0) return IWFPM_ERR_UNSUPPORTED;  // five-pass grids: apply one by one
-        if (p->few_modes[prec]) continue;
+        if (!transforms && p->few_modes[prec]) continue;
         for (int ax = 0; ax < p->n; ++ax) maxe = std::max(maxe, axis_class(p->geom, ax));
         if (sc.fused) lds = std::max(lds, lds_fused(p->geom, esz));
         else lds = std::max({lds, lds_slabs(p->geom, sc.pd, esz), lds_columns(p->geom, sc.pd, esz)});
@@ -112,6 +113,7 @@ int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_
     if (!b) return IWFPM_ERR_ALLOC;
     b->B = B;
     b->prec = prec;
+    b->all_transforms = transforms;
     b->device = dev;
     b->plans.assign(plans, plans + B);
     b->maxs = extent_class_of(maxe);
@@ -121,7 +123,7 @@ int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_
     for (int i = 0; i < B; ++i) {
         const iwfpm_plan_s* p = plans[i];
         items[i].kind = -1;
-        if (!p->few_modes[prec]) {
+        if (!b->few_of(p)) {
             b->transforms = true;
             continue;
         }
@@ -157,6 +159,12 @@ int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_
     return IWFPM_OK;
 }
 
+extern "C" {
+
+int iwfpm_batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_graph, iwfpm_batch_t* out) {
+    return batch_create(B, plans, precision, use_graph, false, out);
+}
+
 int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi, const int* nvec, void* stream) {
     if (!b || !psi || !hpsi || !nvec) return IWFPM_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
@@ -165,7 +173,7 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
     for (int i = 0; i < b->B; ++i) {
         if (nvec[i] < 0 || (nvec[i] > 0 && (!psi[i] || !hpsi[i]))) return IWFPM_ERR_ARG;
         if (nvec[i] > 0) {
-            int rc = plan_ensure_ws(b->plans[i], nvec[i], b->prec, st);
+            int rc = plan_ensure_ws(b->plans[i], nvec[i], b->prec, st, b->all_transforms);
             if (rc) return rc;
         }
     }
@@ -178,11 +186,11 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
     int* start = reinterpret_cast<int*>(b->h_table + b->start_off);
     double few_points = 0.0;
     for (int i = 0; i < b->B; ++i)
-        if (b->plans[i]->few_modes[b->prec]) few_points += (double)b->plans[i]->geom.N * nvec[i];
+        if (b->few_of(b->plans[i])) few_points += (double)b->plans[i]->geom.N * nvec[i];
     for (int i = 0; i < b->B; ++i) {
         iwfpm_plan_s* p = b->plans[i];
         few[i].kind = -1;
-        if (p->few_modes[b->prec]) {
+        if (b->few_of(p)) {
             FewItem& f = few[i];
             std::memset(&f, 0, sizeof(f));
             f.g = p->geom;

@@ -1980,8 +1980,6 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
         if (!b.p->sched[b.prec].ok) b.prec = 1 - b.prec;
         if (!b.p->sched[b.prec].ok) return IWFPM_ERR_UNSUPPORTED;
         b.can64 = b.p->sched[0].ok;
-        // few-mode applies are float64 in either precision: nothing to switch
-        if (b.can64 && b.p->few_modes[0] && b.p->few_modes[1]) b.prec = 0;
         b.hnorm = b.p->lam_max + b.p->vsum_abs;
         b.floor32 = 30.0 * 6e-8 * b.p->vsum_abs / b.hnorm;
         b.eta.assign(m, 1.0);
@@ -2009,12 +2007,17 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
             bool ok = true;
             // plans on the five-pass schedule are applied one by one
             for (auto* p : pl) ok = ok && p->sched[k].ok && (p->sched[k].fused || p->sched[k].pd.split_mid == 0);
-            if (ok && (rc = iwfpm_batch_create(B, pl.data(), k == 1 ? IWFPM_PREC_FP32 : IWFPM_PREC_FP64, 1, &bat[k])))
+            if (ok &&
+                (rc = batch_create(B, pl.data(), k == 1 ? IWFPM_PREC_FP32 : IWFPM_PREC_FP64, 1, true, &bat[k])))
                 return rc;
         }
     }
     auto V = [&](BInst& b, int buf, int v0, int cnt) { return Rt::vecs(b.c, buf, v0, cnt); };
-    // H applied to the first cnt[i] trial vectors of bin into bout, by precision
+    // H applied to the first cnt[i] trial vectors of bin into bout, by precision.
+    // Always by the transforms: a solve stops when its residuals pass, and where
+    // the wanted pairs end inside a cluster the values it stops at move by up to
+    // (tol ||H||)^2 / gap with any change of the applies' rounding (1e-6 of the
+    // eigenvalues seen at tol = 1e-8 on 24^2 x 32^2 points, lambda = 2).
     auto apply_all = [&](int bin, int bout, const std::vector<int>& cnt, const std::vector<int>& precs) -> int {
         for (int k = 0; k < 2; ++k) {
             std::vector<const void*> x(B, nullptr);
@@ -2032,7 +2035,7 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
             if (!any) continue;
             if (!bat[k]) {
                 for (int i = 0; i < B; ++i)
-                    if (nv[i] && (rc = plan_apply(in[i].p, x[i], y[i], nv[i], k, st))) return rc;
+                    if (nv[i] && (rc = plan_apply(in[i].p, x[i], y[i], nv[i], k, st, 1, true))) return rc;
                 continue;
             }
             if ((rc = iwfpm_batch_apply(bat[k], x.data(), y.data(), nv.data(), st))) return rc;
@@ -2193,7 +2196,7 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
         for (int i : iter) {
             BInst& b = in[i];
             ++b.it;
-            if (b.prec == 0 && b.p->opts.precision == 1 && !b.p->few_modes[1]) ++b.polished;
+            if (b.prec == 0 && b.p->opts.precision == 1) ++b.polished;
             // active set: the pairs not yet converged (soft locking)
             b.act.clear();
             for (int j = 0; j < m; ++j)

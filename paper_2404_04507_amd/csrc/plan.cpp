@@ -365,8 +365,6 @@ static int build_potential(iwfpm_plan_s* p, int n_modes, const int32_t* modes, c
     } else {
         p->geom.vmode = 1;
         p->vtab.clear();
-        p->vgrid.clear();
-        if (p->few_modes[0] && p->few_modes[1]) return IWFPM_OK;  // only the transforms read it
         p->vgrid.assign(g.N, 0.0);
         std::vector<int> l(n);
         for (long long gp = 0; gp < g.N; ++gp) {
@@ -951,10 +949,10 @@ static hipError_t launch_sched(const Schedule& sc, const DevGeom& g, const DevTa
 
 static const size_t kWorkspaceCap = (size_t)4 << 30;
 
-int plan_ensure_ws(iwfpm_plan_s* p, int nvec, int prec, hipStream_t st) {
+int plan_ensure_ws(iwfpm_plan_s* p, int nvec, int prec, hipStream_t st, bool transforms) {
     const Schedule& sc = p->sched[prec];
     if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
-    if (sc.fused || p->few_modes[prec]) return IWFPM_OK;
+    if (sc.fused || (p->few_modes[prec] && !transforms)) return IWFPM_OK;
     size_t need = (size_t)p->geom.N * (prec ? 8 : 16) * nvec;
     if (p->d_ws.bytes < need) {
         if (hipStreamSynchronize(st) != hipSuccess) return IWFPM_ERR_DEVICE;
@@ -964,12 +962,12 @@ int plan_ensure_ws(iwfpm_plan_s* p, int nvec, int prec, hipStream_t st) {
 }
 
 int plan_apply_ws(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int precision, hipStream_t st,
-                  int kinetic, void* ws, size_t ws_bytes) {
+                  int kinetic, void* ws, size_t ws_bytes, bool transforms) {
     if (nvec == 0) return IWFPM_OK;
     const int prec = precision == IWFPM_PREC_FP32 ? 1 : 0;
     const Schedule& sc = p->sched[prec];
     if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
-    if (p->few_modes[prec]) {
+    if (p->few_modes[prec] && !transforms) {
         // float64 throughout at the same cost as float32, and no workspace
         DevGeom g = p->geom;
         g.kin = kinetic ? 1 : 0;
@@ -1001,12 +999,13 @@ int plan_apply_ws(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int pr
     return IWFPM_OK;
 }
 
-int plan_apply(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int precision, hipStream_t st, int kinetic) {
+int plan_apply(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int precision, hipStream_t st, int kinetic,
+               bool transforms) {
     if (nvec == 0) return IWFPM_OK;
     const int prec = precision == IWFPM_PREC_FP32 ? 1 : 0;
     const Schedule& sc = p->sched[prec];
     if (!sc.ok) return IWFPM_ERR_UNSUPPORTED;
-    if (!sc.fused && !p->few_modes[prec]) {
+    if (!sc.fused && (transforms || !p->few_modes[prec])) {
         // the plan's own workspace, grown to the vectors of one chunk
         const size_t per = (size_t)p->geom.N * (prec ? 8 : 16);
         const int chunk = (int)std::max<size_t>(1, std::min<size_t>((size_t)nvec, kWorkspaceCap / per));
@@ -1015,9 +1014,9 @@ int plan_apply(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int preci
             if (hipStreamSynchronize(st) != hipSuccess) return IWFPM_ERR_DEVICE;
             if (dev_alloc(p->d_ws, need) != IWFPM_OK) return IWFPM_ERR_ALLOC;
         }
-        return plan_apply_ws(p, psi, hpsi, nvec, precision, st, kinetic, p->d_ws.ptr, need);
+        return plan_apply_ws(p, psi, hpsi, nvec, precision, st, kinetic, p->d_ws.ptr, need, transforms);
     }
-    return plan_apply_ws(p, psi, hpsi, nvec, precision, st, kinetic, nullptr, 0);
+    return plan_apply_ws(p, psi, hpsi, nvec, precision, st, kinetic, nullptr, 0, transforms);
 }
 
 }  // namespace iwfpm
@@ -1291,17 +1290,14 @@ int iwfpm_tune(iwfpm_plan_t p, int nvec, int precision, void* stream, double* be
     hipStream_t st = (hipStream_t)stream;
     std::vector<Schedule> cands = schedule_candidates(p, prec);
     if (cands.empty()) return IWFPM_ERR_UNSUPPORTED;
-    // the few-mode convolution has no schedule to choose: it is timed alone
-    const bool few = p->few_modes[prec];
-    if (few) cands.assign(1, p->sched[prec]);
-    if (!few && cands.size() == 1 && !cands[0].fused && cands[0].pd.split_mid > 0) {
+    if (cands.size() == 1 && !cands[0].fused && cands[0].pd.split_mid > 0) {
         p->sched[prec] = cands[0];  // the one five-pass schedule: nothing to choose
         if (best_us) *best_us = -1.0;
         return IWFPM_OK;
     }
     const std::string key = tune_key(p, prec, nvec);
     const char* cache = std::getenv("IWFPM_TUNE_CACHE");
-    if (!few && cache && cache[0]) {
+    if (cache && cache[0]) {
         Schedule sc{};
         if (tune_cache_lookup(cache, key, sc, p, prec)) {
             if (sc.fused) {
@@ -1334,10 +1330,11 @@ int iwfpm_tune(iwfpm_plan_t p, int nvec, int precision, void* stream, double* be
     int rc = IWFPM_OK;
     for (const Schedule& c : cands) {
         p->sched[prec] = c;
-        if ((rc = plan_apply(p, x.ptr, y.ptr, nvec, prec, st)) != IWFPM_OK) break;
+        if ((rc = plan_apply(p, x.ptr, y.ptr, nvec, prec, st, 1, true)) != IWFPM_OK) break;
         (void)hipEventRecord(e0, st);
         const int reps = 3;
-        for (int r = 0; r < reps && rc == IWFPM_OK; ++r) rc = plan_apply(p, x.ptr, y.ptr, nvec, prec, st);
+        for (int r = 0; r < reps && rc == IWFPM_OK; ++r)
+            rc = plan_apply(p, x.ptr, y.ptr, nvec, prec, st, 1, true);
         (void)hipEventRecord(e1, st);
         if (hipEventSynchronize(e1) != hipSuccess) rc = IWFPM_ERR_DEVICE;
         if (rc != IWFPM_OK) break;
@@ -1360,7 +1357,7 @@ int iwfpm_tune(iwfpm_plan_t p, int nvec, int precision, void* stream, double* be
     }
     p->sched[prec] = best_sc;
     if (best_us) *best_us = best;
-    if (!few && cache && cache[0]) {
+    if (cache && cache[0]) {
         if (FILE* f = std::fopen(cache, "a")) {
             std::fprintf(f, "%s %d %d %d %d %.3f %d\n", key.c_str(), best_sc.fused ? 1 : 0, best_sc.pd.split,
                          best_sc.pd.tile, best_sc.pd.slabs_per_wg, best, best_sc.pd.threads_outer);

@@ -106,7 +106,8 @@ int dev_alloc(DeviceBuf& b, size_t bytes);
 void dev_free(DeviceBuf& b);
 
 // grow the plan's apply workspace for nvec vectors of precision prec
-int plan_ensure_ws(iwfpm_plan_s* p, int nvec, int prec, hipStream_t st);
+// (transforms: for the transform route also where the plan takes the few-mode one)
+int plan_ensure_ws(iwfpm_plan_s* p, int nvec, int prec, hipStream_t st, bool transforms = false);
 int extent_class_of(int e);
 // stages of an axis transform (fac[0..return)), 0 if the extent is unsupported
 int axis_factors(int e, int* fac);
@@ -115,12 +116,16 @@ int axis_class(const DevGeom& g, int ax);
 
 // apply on a plan (precision 0 = float64 convolution, 1 = float32), with the
 // plan's own workspace (grown as needed)
-int plan_apply(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int precision, hipStream_t st, int kinetic = 1);
+int plan_apply(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int precision, hipStream_t st, int kinetic = 1,
+               bool transforms = false);
 // the same with a caller's workspace of ws_bytes (vectors applied in chunks
 // whose intermediate grids fit; ERR_ARG if one vector's does not); allocates
 // nothing
 int plan_apply_ws(iwfpm_plan_s* p, const void* psi, void* hpsi, int nvec, int precision, hipStream_t st,
-                  int kinetic, void* ws, size_t ws_bytes);
+                  int kinetic, void* ws, size_t ws_bytes, bool transforms = false);
+
+// iwfpm_batch_create; transforms: no plan takes the few-mode route
+int batch_create(int B, const iwfpm_plan_t* plans, int precision, int use_graph, bool transforms, iwfpm_batch_t* out);
 
 // grid position -> true label k (paper order) and vector position
 void host_label(const iwfpm_plan_s* p, long long gpos, int* k_out);
