@@ -1001,21 +1001,21 @@ static int rr_coefficients_t(const std::vector<S>& G, const std::vector<double>&
     std::vector<S> Z((size_t)ns * m, 0.0);
     for (int a = 0; a < ma; ++a)
         for (int i = m; i < ns; ++i) Z[i + (size_t)a * ns] = Cfull[i + (size_t)act[a] * ns];
-    auto project = [&](std::vector<S>& B, int nb) {  // B <- B - C_x (C_x^H B)
-        std::vector<S> Gx((size_t)m * std::max(nb, 1), 0.0);
-        for (int j = 0; j < nb; ++j)
+    for (int pass = 0; pass < 2; ++pass) {
+        std::vector<S> Gx((size_t)m * m, 0.0);  // C_x^H Z
+        for (int j = 0; j < ma; ++j)
             for (int i = 0; i < m; ++i) {
                 S acc = 0.0;
-                for (int k = 0; k < ns; ++k) acc += conj_(Cfull[k + (size_t)i * ns]) * B[k + (size_t)j * ns];
+                for (int k = 0; k < ns; ++k) acc += conj_(Cfull[k + (size_t)i * ns]) * Z[k + (size_t)j * ns];
                 Gx[i + (size_t)j * m] = acc;
             }
-        for (int j = 0; j < nb; ++j)
-            for (int i = 0; i < m; ++i) {
-                const S x = Gx[i + (size_t)j * m];
-                for (int k = 0; k < ns; ++k) B[k + (size_t)j * ns] -= Cfull[k + (size_t)i * ns] * x;
+        for (int j = 0; j < ma; ++j)
+            for (int k = 0; k < ns; ++k) {
+                S acc = 0.0;
+                for (int i = 0; i < m; ++i) acc += Cfull[k + (size_t)i * ns] * Gx[i + (size_t)j * m];
+                Z[k + (size_t)j * ns] -= acc;
             }
-    };
-    for (int pass = 0; pass < 2; ++pass) project(Z, ma);
+    }
     int mpn = 0;
     U.assign((size_t)ns * (2 * m), 0.0);
     for (int j = 0; j < m; ++j)
@@ -1032,30 +1032,12 @@ static int rr_coefficients_t(const std::vector<S>& G, const std::vector<double>&
         for (int j = 0; j < ma; ++j) gmax = std::max(gmax, real_(Gz[j + (size_t)j * ma]));
         if (gmax > 1e-28) {
             mpn = svqb_t(Gz, ma, T, 1e-12);
-            std::vector<S> Q((size_t)ns * std::max(mpn, 1), 0.0);
             for (int j = 0; j < mpn; ++j)
-                for (int k = 0; k < ma; ++k)
-                    for (int i = 0; i < ns; ++i) Q[i + (size_t)j * ns] += Z[i + (size_t)k * ns] * T[k + (size_t)j * ma];
-            // Once more: the kept directions' scaled eigenvalues reach down to
-            // 1e-12, so one pass leaves P orthonormal only to about 1e-16 over
-            // that (1e-5 seen on a 9-vector block with pairs 2e-6 apart), and
-            // the loss passes into the next X (5e-8 after 60 iterations, where
-            // the Ritz values fall below the exact ones and the solve stalls).
-            project(Q, mpn);
-            std::vector<S> Gq((size_t)mpn * mpn, 0.0), T2;
-            for (int j = 0; j < mpn; ++j)
-                for (int i = 0; i < mpn; ++i) {
+                for (int i = 0; i < ns; ++i) {
                     S acc = 0.0;
-                    for (int k = 0; k < ns; ++k) acc += conj_(Q[k + (size_t)i * ns]) * Q[k + (size_t)j * ns];
-                    Gq[i + (size_t)j * mpn] = acc;
+                    for (int k = 0; k < ma; ++k) acc += Z[i + (size_t)k * ns] * T[k + (size_t)j * ma];
+                    U[i + (size_t)(m + j) * ns] = acc;
                 }
-            hermitian_part(Gq, mpn);
-            const int mq = mpn;
-            mpn = mq > 0 ? svqb_t(Gq, mq, T2, 1e-12) : 0;
-            for (int j = 0; j < mpn; ++j)
-                for (int k = 0; k < mq; ++k)
-                    for (int i = 0; i < ns; ++i)
-                        U[i + (size_t)(m + j) * ns] += Q[i + (size_t)k * ns] * T2[k + (size_t)j * mq];
         }
     }
     return mpn;
@@ -1069,12 +1051,6 @@ static int rr_coefficients(const std::vector<cd>& G, const std::vector<double>& 
     U = as_complex(u);
     return mpn;
 }
-
-// Scaled eigenvalue below which a direction of W is dropped.  The Gram it is
-// taken from carries rounding of some 1e-15, so the kept directions come out
-// orthonormal to 1e-15 over this; a direction dropped here returns with the
-// next residual.  (At 1e-10 the basis was orthonormal to 1e-5 at times.)
-constexpr double kOrthoDrop = 1e-6;
 
 // Second projection and orthonormalisation of the new directions W (ma
 // columns) against the orthonormal [X P] (nx columns), in coefficient space,
@@ -1108,7 +1084,7 @@ static bool ortho_coefficients_t(const std::vector<S>& Gall, int nx, int ma, std
         if (!std::isfinite(real_(Gc[j + (size_t)j * ma])) || !(real_(Gc[j + (size_t)j * ma]) > 0.0)) return false;
     hermitian_part(Gc, ma);
     std::vector<S> T;
-    mw = svqb_t(Gc, ma, T, kOrthoDrop);
+    mw = svqb_t(Gc, ma, T, 1e-10);
     if (mw < 1) return false;
     Cm.assign((size_t)ld * mw, 0.0);
     for (int c = 0; c < mw; ++c) {
@@ -2308,7 +2284,7 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
                 parallel_for((int)two.size(), [&](int u) {
                     BInst& b = in[iter[two[u]]];
                     if (Rt::real) hermitian_part(G[u], b.ma);
-                    b.mw = svqb(G[u], b.ma, b.T, kOrthoDrop);
+                    b.mw = svqb(G[u], b.ma, b.T, 1e-10);
                 });
                 std::vector<LinQ<Rt>> l2;
                 for (size_t k : two) {
