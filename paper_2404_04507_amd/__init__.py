@@ -178,8 +178,10 @@ def _ptr(a, t):
 def _stream_handle(stream):
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(stream.cuda_stream))
+        # the current stream's handle without the Stream object around it
+        # (0.4 against 2.7 us, a fifth of a small apply)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return int(stream.cuda_stream)
 
 
 def dense_geneig(A, B=None):
@@ -466,7 +468,7 @@ class Plan:
             raise TypeError("vectors must be complex128 CUDA tensors")
         if x.shape[-1] != self.N or not x.is_contiguous():
             raise ValueError(f"vectors must be contiguous with last dimension N={self.N}")
-        return 1 if x.dim() == 1 else int(np.prod(x.shape[:-1]))
+        return x.numel() // self.N
 
     def apply(self, psi, out=None, precision=None, stream=None):
         """H psi; psi (nvec, N) or (N,) complex128 on the plan's GPU."""

@@ -2521,7 +2521,6 @@ int iwfpm_destroy(iwfpm_plan_t p) {
         DeviceGuard g(p->opts.device);
         (void)hipDeviceSynchronize();
         dev_free(p->d_slice_a);
-        dev_free(p->d_slice_m);
         dev_free(p->d_slice_g);
         dev_free(p->d_vtab32);
         dev_free(p->d_vtab64);

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 
@@ -812,7 +813,21 @@ static int prepare_kernels() {
     e = prepare_batch<R, 16>(b); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
     e = prepare_batch<R, 32>(b); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
     e = prepare_batch<R, 64>(b); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
-    e = prepare_stencil(); if (e != hipSuccess) return IWFPM_ERR_DEVICE;
+    return IWFPM_OK;
+}
+
+// The kernels' dynamic-LDS limits, raised once per device (37 calls, some 150 us).
+static int prepare_device(int dev) {
+    static std::mutex mu;
+    static std::vector<char> done;
+    std::lock_guard<std::mutex> lock(mu);
+    if (dev < (int)done.size() && done[dev]) return IWFPM_OK;
+    int rc = prepare_kernels<float>();
+    if (rc == IWFPM_OK) rc = prepare_kernels<double>();
+    if (rc == IWFPM_OK && prepare_stencil() != hipSuccess) rc = IWFPM_ERR_DEVICE;
+    if (rc != IWFPM_OK) return rc;
+    if (dev >= (int)done.size()) done.resize(dev + 1, 0);
+    done[dev] = 1;
     return IWFPM_OK;
 }
 
@@ -828,14 +843,14 @@ static int upload(DeviceBuf& b, const std::vector<T>& v) {
 
 static int upload_tables(iwfpm_plan_s* p) {
     int rc;
-    if ((rc = upload(p->d_slice_a, p->slice_a)) != IWFPM_OK) return rc;
-    if ((rc = upload(p->d_slice_g, p->slice_g)) != IWFPM_OK) return rc;
-    std::vector<int> am(p->slice_a.size());
-    for (size_t e = 0; e < am.size(); ++e) {
+    // the window ends, then the same modulo their axis' extent
+    std::vector<int> ends(p->slice_a);
+    for (size_t e = 0; e < p->slice_a.size(); ++e) {
         const int E = p->geom.ext[p->n - p->d + (int)(e % p->d)];
-        am[e] = ((p->slice_a[e] % E) + E) % E;
+        ends.push_back(((p->slice_a[e] % E) + E) % E);
     }
-    if ((rc = upload(p->d_slice_m, am)) != IWFPM_OK) return rc;
+    if ((rc = upload(p->d_slice_a, ends)) != IWFPM_OK) return rc;
+    if ((rc = upload(p->d_slice_g, p->slice_g)) != IWFPM_OK) return rc;
     std::vector<float> f32;
     if (!p->vtab.empty()) {
         if ((rc = upload(p->d_vtab64, p->vtab)) != IWFPM_OK) return rc;
@@ -855,7 +870,7 @@ static int upload_tables(iwfpm_plan_s* p) {
     p->tabs.tw32 = (const float*)p->d_tw32.ptr;
     p->tabs.tw64 = (const double*)p->d_tw64.ptr;
     p->tabs.slice_a = (const int*)p->d_slice_a.ptr;
-    p->tabs.slice_m = (const int*)p->d_slice_m.ptr;
+    p->tabs.slice_m = p->tabs.slice_a + p->slice_a.size();
     p->tabs.slice_g = (const double*)p->d_slice_g.ptr;
     p->tabs.vtab32 = (const float*)p->d_vtab32.ptr;
     p->tabs.vtab64 = (const double*)p->d_vtab64.ptr;
@@ -1122,8 +1137,7 @@ int iwfpm_plan(int d, int n, const double* P, const int32_t* K, const int32_t* L
             delete p;
             return IWFPM_ERR_DEVICE;
         }
-        rc = prepare_kernels<float>();
-        if (rc == IWFPM_OK) rc = prepare_kernels<double>();
+        rc = prepare_device(o.device);
         if (rc == IWFPM_OK) rc = upload_tables(p);
         if (rc != IWFPM_OK) {
             iwfpm_destroy(p);

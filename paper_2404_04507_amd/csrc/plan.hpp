@@ -76,7 +76,7 @@ struct iwfpm_plan_s {
     iwfpm::Schedule sched[2];
     // device
     bool host_only = true;
-    iwfpm::DeviceBuf d_slice_a, d_slice_m, d_slice_g, d_vtab32, d_vtab64, d_vgrid32, d_vgrid64, d_tw32, d_tw64;
+    iwfpm::DeviceBuf d_slice_a, d_slice_g, d_vtab32, d_vtab64, d_vgrid32, d_vgrid64, d_tw32, d_tw64;
     iwfpm::DeviceBuf d_ws;        // apply workspace
     iwfpm::DeviceBuf d_ef_freq;   // eigenfunction output: (P k)_j per window point (d x N)
     iwfpm::DeviceBuf d_ef_ws;     // eigenfunction output: per-axis tables and slice partials
@@ -95,7 +95,8 @@ struct DeviceGuard {
     bool ok = true;
     explicit DeviceGuard(int dev) {
         if (hipGetDevice(&prev) != hipSuccess) prev = -1;
-        ok = hipSetDevice(dev) == hipSuccess;
+        if (prev == dev) prev = -1;  // nothing to set, nothing to restore
+        else ok = hipSetDevice(dev) == hipSuccess;
     }
     ~DeviceGuard() {
         if (prev >= 0) (void)hipSetDevice(prev);
