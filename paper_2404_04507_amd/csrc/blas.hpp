@@ -20,9 +20,17 @@ struct Reals {
     double v[kMaxCols];
 };
 
-// C (p x q, column-major, C[j*p + i]) = L^H R; `partial` holds max_blocks*p*q entries
+// A reduction's end, seen from the host: it writes its results to pinned host
+// memory and then seq to the pinned flag.
+struct Done {
+    unsigned* flag;
+    unsigned seq;
+};
+
+// C (p x q, column-major, C[j*p + i]) = L^H R; `partial` holds max_blocks*p*q entries.
+// done (here and below): raise its flag when C is written
 hipError_t gram(const ColPtrs& L, int p, const ColPtrs& R, int q, long long N, double2* partial, int max_blocks,
-                double2* C, hipStream_t st);
+                double2* C, hipStream_t st, const Done* done = nullptr);
 // Y_j = beta Y_j + sum_i A_i C[j*p + i], q <= 48
 hipError_t lincomb(const ColPtrs& A, int p, const ColPtrs& Y, int q, const double2* C, double beta, long long N,
                    hipStream_t st);
@@ -36,11 +44,20 @@ hipError_t lincomb(const ColPtrs& A, int p, const ColPtrs& Y, int q, const doubl
 //                  when M is not null, into ceil(n/2) columns (a zero half when n is odd)
 //   unpack_real    complex column v = (real vector v, 0)
 hipError_t gram_pairs(const ColPtrs& L, int p, const ColPtrs& R, int q, long long N, double2* partial, int max_blocks,
-                      double* C, hipStream_t st);
+                      double* C, hipStream_t st, const Done* done = nullptr);
 hipError_t lincomb_pairs(const ColPtrs& A, int p, const ColPtrs& Y, int q, const double* C, double beta, long long N,
                          hipStream_t st);
 hipError_t residual_norm_pairs(const ColPtrs& HX, const ColPtrs& X, const ColPtrs& R, const Reals& theta, int m,
-                               long long N, double* partial, int max_blocks, double* out, hipStream_t st);
+                               long long N, double* partial, int max_blocks, double* out, hipStream_t st,
+                               const Done* done = nullptr);
+// lincomb_pairs for one or two sets (A, Y) with the same host coefficients,
+// passed by value: p, q <= kSmallP, 4 p q <= kCoefArg
+constexpr int kSmallP = 16, kCoefArg = 256;
+struct SmallCols {
+    double2* p[kSmallP];
+};
+hipError_t lincomb_pairs_small(const SmallCols* A, int p, const SmallCols* Y, int q, int sets, const double* C,
+                               double beta, long long N, hipStream_t st);
 hipError_t gather_pairs(const ColPtrs& src, unsigned long long parts, int n, const ColPtrs& dst, const double* M,
                         long long N, hipStream_t st);
 hipError_t unpack_real(const ColPtrs& src, unsigned long long parts, int n, const ColPtrs& dst, long long N,
@@ -52,7 +69,8 @@ hipError_t colnorm2(const ColPtrs& V, int m, long long N, double* partial, int m
                     hipStream_t st);
 // R_j = HX_j - theta_j X_j and out[j] = ||R_j||^2
 hipError_t residual_norm(const ColPtrs& HX, const ColPtrs& X, const ColPtrs& R, const Reals& theta, int m, long long N,
-                         double* partial, int max_blocks, double* out, hipStream_t st);
+                         double* partial, int max_blocks, double* out, hipStream_t st,
+                         const Done* done = nullptr);
 hipError_t precond(const ColPtrs& R, const ColPtrs& W, int m, const double* M, long long N, hipStream_t st);
 hipError_t randn(double2* out, long long count, unsigned long long seed, hipStream_t st);
 

@@ -56,9 +56,10 @@ __device__ __forceinline__ void gram_load(const double2* lp, const double2* cons
 // (rr, ri, ir, ii), written as real (2p x 2q, column-major) partials.
 template <int TQ, bool PAIRS = false>
 __device__ __forceinline__ void gram_body(const ColPtrs& L, int p, const ColPtrs& R, int q, long long N,
-                                          long long groups_per_block, double2* __restrict__ partial, int bid) {
+                                          long long groups_per_block, double2* __restrict__ partial, int bid,
+                                          int wave) {
     constexpr int D = kGramDepth;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     const int li = lane & 15, lk = lane >> 4;
     const int cl = 16 * wave + li;
     const double2* lp = cl < p ? L.p[cl] : nullptr;
@@ -146,13 +147,13 @@ __device__ __forceinline__ void gram_body(const ColPtrs& L, int p, const ColPtrs
 template <int TQ>
 __global__ void __launch_bounds__(256) k_gram(ColPtrs L, int p, ColPtrs R, int q, long long N, long long groups_per_block,
                                               double2* __restrict__ partial) {
-    gram_body<TQ>(L, p, R, q, N, groups_per_block, partial, blockIdx.x);
+    gram_body<TQ>(L, p, R, q, N, groups_per_block, partial, blockIdx.x, threadIdx.x >> 6);
 }
 
 template <int TQ>
 __global__ void __launch_bounds__(256) k_gram_pairs(ColPtrs L, int p, ColPtrs R, int q, long long N,
                                                     long long groups_per_block, double2* __restrict__ partial) {
-    gram_body<TQ, true>(L, p, R, q, N, groups_per_block, partial, blockIdx.x);
+    gram_body<TQ, true>(L, p, R, q, N, groups_per_block, partial, blockIdx.x, threadIdx.x >> 6);
 }
 
 // C[e] = sum over the nb partials, one workgroup per entry, fixed summation order
@@ -179,6 +180,92 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const double2* __restri
 }
 
 // ---------------------------------------------------------------------------
+// Small solves are bound by launches and round trips: few partials are summed by
+// one workgroup, which writes them to pinned host memory and then raises a flag
+// there; the host waits on that instead of on the stream (7 against 11 us a
+// round trip, and 20 us more for a stream that has taken many launches since it
+// was last waited on).  The rows of every block and the order of every sum are
+// those of the kernels these stand for, and so are the results' bits.  Summing
+// in the Gram itself was slower: by its last block to finish 22 us a Gram
+// against 5 and 4 (the fences between the XCDs' L2s), in one workgroup 24 us.
+// An iteration of a 1D solve (fp64), before and after: N = 1000, 1 to 4 vectors
+// 122..130 -> 95..101 us; N = 2400 127..135 -> 105..115 us; N = 20000 180..190
+// -> 158..170 us; 8 to 16 vectors 160..364 -> 143..360 us.
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallSums = 4096;       // half the partials that one workgroup sums (64 KB of LDS)
+constexpr int kSmallCols = 4;          // columns of a small residual
+
+// sum over b of v[b] (b < nb, 0 past it) as k_reduce_partials and k_reduce_real
+// form it: thread t of 256 adds b = t, t + 256, ..., then halves add up.  One
+// wave; lane 0 has the result.
+template <typename F>
+__device__ __forceinline__ double wave_tree(int nb, F&& v) {
+    const int lane = threadIdx.x & 63;
+    double s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        s[j] = 0.0;
+        for (int b = lane + 64 * j; b < nb; b += 256) s[j] += v(b);
+    }
+    double r = (s[0] + s[2]) + (s[1] + s[3]);
+    for (int w = 32; w > 0; w >>= 1) r += __shfl_down(r, w, 64);
+    return r;
+}
+
+// the first wave writes the workgroup's results (in LDS, after a barrier) to the
+// host and raises the flag: one wave, since a fence for the host's eyes costs
+// a write-back of the L2 in each wave that has one
+__device__ __forceinline__ void publish(const double2* res, int n, double2* __restrict__ out, const Done& done) {
+    if (threadIdx.x >= 64) return;
+    for (int e = threadIdx.x; e < n; e += 64) out[e] = res[e];
+    __threadfence_system();
+    if (threadIdx.x == 0) __hip_atomic_store(done.flag, done.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// k_reduce_partials for few partials, in one workgroup: its tree over the blocks
+// for all entries at a time (a wave per entry took 8.7 us for 16 x 64, this 5),
+// whose upper half is added as it is read
+__global__ void __launch_bounds__(kSmallThreads) k_reduce_small(const double2* __restrict__ partial, int nb, int count,
+                                                                double2* __restrict__ C, Done done) {
+    __shared__ double2 v[kSmallSums];
+    const int n = nb * count;
+    int w = 1;
+    while (w < 128 && 2 * w < nb) w *= 2;
+    const auto column = [&](int i) {
+        double2 s = make_double2(0.0, 0.0);
+        for (; i < n; i += 256 * count) {
+            const double2 x = partial[i];
+            s.x += x.x;
+            s.y += x.y;
+        }
+        return s;
+    };
+#pragma unroll 4
+    for (int i = threadIdx.x; i < w * count; i += kSmallThreads) {
+        const double2 x = column(i), y = column(i + w * count);
+        v[i] = make_double2(x.x + y.x, x.y + y.y);
+    }
+    __syncthreads();
+    for (w >>= 1; w > 0; w >>= 1) {
+        for (int i = threadIdx.x; i < w * count; i += kSmallThreads) {
+            v[i].x += v[i + w * count].x;
+            v[i].y += v[i + w * count].y;
+        }
+        __syncthreads();
+    }
+    publish(v, count, C, done);
+}
+
+// the flag alone, after reductions of many partials: what ran before it on the
+// stream is in memory
+__global__ void __launch_bounds__(64) k_done(Done done) {
+    if (threadIdx.x > 0) return;
+    __threadfence_system();
+    __hip_atomic_store(done.flag, done.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// ---------------------------------------------------------------------------
 // lincomb, q <= 32: the four wavefronts of a workgroup share a pair of 64-row
 // strips (rows r and r + 64 per lane) and split the outputs, wave w taking
 // columns [w qg, w qg + qg) with qg = ceil(q / 4).  C (column-major, C[j*p + i])
@@ -189,8 +276,8 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const double2* __restri
 // PAIRS: A and Y hold two real vectors per complex column and C is the real
 // (2p x 2q, column-major) coefficient matrix: each (input, output) column pair
 // takes a 2 x 2 real block.
-template <int QG, bool PAIRS = false>
-__device__ __forceinline__ void lincomb_rows_body(const ColPtrs& A, int p, const ColPtrs& Y, int q,
+template <int QG, bool PAIRS = false, class Cols = ColPtrs>
+__device__ __forceinline__ void lincomb_rows_body(const Cols& A, int p, const Cols& Y, int q,
                                                   const double2* __restrict__ C, double beta, long long N, int bid,
                                                   int nb) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -271,6 +358,20 @@ template <int QG>
 __global__ void __launch_bounds__(256) k_lincomb_pairs(ColPtrs A, int p, ColPtrs Y, int q,
                                                        const double2* __restrict__ C, double beta, long long N) {
     lincomb_rows_body<QG, true>(A, p, Y, q, C, beta, N, blockIdx.x, gridDim.x);
+}
+
+// Small combinations: few coefficients travel with the launch instead of by a
+// copy before it, and two with the same coefficients share one (blockIdx.y).
+struct CoefArg {
+    double v[kCoefArg];
+};
+template <int QG>
+__global__ void __launch_bounds__(256) k_lincomb_pairs_small(SmallCols A0, SmallCols A1, int p, SmallCols Y0,
+                                                             SmallCols Y1, int q, CoefArg C, double beta,
+                                                             long long N) {
+    const double2* c = reinterpret_cast<const double2*>(C.v);
+    if (blockIdx.y == 0) lincomb_rows_body<QG, true>(A0, p, Y0, q, c, beta, N, blockIdx.x, gridDim.x);
+    else lincomb_rows_body<QG, true>(A1, p, Y1, q, c, beta, N, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -497,6 +598,45 @@ __device__ __forceinline__ void residual_norm_pairs_body(const ColPtrs& HX, cons
     }
 }
 
+// the same for up to 2,048 rows (at most two to a block: thread 0's and thread
+// 1's), blocks and order of the sums as in the two kernels it stands for
+__global__ void __launch_bounds__(kSmallThreads) k_residual_small(ColPtrs HX, ColPtrs X, ColPtrs Rout, Reals theta,
+                                                                  int m, int N, int rpb, double* __restrict__ out,
+                                                                  Done done) {
+    __shared__ double part[2 * kSmallCols][kSmallThreads];
+    __shared__ double2 res[kSmallCols];
+    const int b = threadIdx.x, nb = (N + rpb - 1) / rpb;
+    if (b < nb) {
+#pragma unroll
+        for (int j = 0; j < kSmallCols; ++j) {
+            if (j >= m) break;
+            const double t0 = theta.v[2 * j], t1 = theta.v[2 * j + 1];
+            double p0 = 0.0, p1 = 0.0;
+            for (int i = 0; i < rpb && b * rpb + i < N; ++i) {
+                const int r = b * rpb + i;
+                const double2 h = HX.p[j][r], x = X.p[j][r];
+                const double2 v = make_double2(h.x - t0 * x.x, h.y - t1 * x.y);
+                Rout.p[j][r] = v;
+                double s0 = 0.0, s1 = 0.0;  // a thread's sum each, rounded before they are added
+                s0 += v.x * v.x;
+                s1 += v.y * v.y;
+                p0 += s0;
+                p1 += s1;
+            }
+            part[2 * j][b] = p0;
+            part[2 * j + 1][b] = p1;
+        }
+    }
+    __syncthreads();
+    const int wave = threadIdx.x >> 6;
+    if (wave < 2 * m) {
+        const double s = wave_tree(nb, [&](int i) { return part[wave][i]; });
+        if ((threadIdx.x & 63) == 0) (&res[0].x)[wave] = s;
+    }
+    __syncthreads();
+    publish(res, m, reinterpret_cast<double2*>(out), done);
+}
+
 __global__ void __launch_bounds__(256) k_residual_norm_pairs(ColPtrs HX, ColPtrs X, ColPtrs Rout, Reals theta, int m,
                                                              long long N, long long rows_per_block,
                                                              double* __restrict__ partial) {
@@ -586,7 +726,8 @@ __global__ void __launch_bounds__(256) k_gram_batched(const GramJob* __restrict_
     const int j = find_job(jobs, njobs, blockIdx.x);
     const GramJob& jb = jobs[j];
     if ((int)(threadIdx.x >> 6) * 16 >= jb.p) return;
-    gram_body<TQ>(jb.L, jb.p, jb.R, jb.q, jb.N, jb.groups_per_block, partial + jb.part_off, blockIdx.x - jb.start);
+    gram_body<TQ>(jb.L, jb.p, jb.R, jb.q, jb.N, jb.groups_per_block, partial + jb.part_off, blockIdx.x - jb.start,
+                  threadIdx.x >> 6);
 }
 
 // one workgroup per output entry over all jobs (job j's entries start at out_start)
@@ -680,7 +821,7 @@ __global__ void __launch_bounds__(256) k_gram_batched_pairs(const GramJob* __res
     const GramJob& jb = jobs[j];
     if ((int)(threadIdx.x >> 6) * 16 >= jb.p) return;
     gram_body<TQ, true>(jb.L, jb.p, jb.R, jb.q, jb.N, jb.groups_per_block, partial + jb.part_off,
-                        blockIdx.x - jb.start);
+                        blockIdx.x - jb.start, threadIdx.x >> 6);
 }
 
 template <int QG>
@@ -748,8 +889,20 @@ static int gram_single_blocks(int p, int per_block, long long N, int max_blocks,
     return gram_job_blocks(p, N, want, gpb);
 }
 
+// the reduction of a Gram's partials: by one workgroup where they are few.  At
+// 8192 of them it takes 5 us, as long as the workgroups of k_reduce_partials and
+// the launch of k_done; at 16384 (16 vectors, N = 1000) an iteration took 3 % more.
+static void reduce_partials(const double2* partial, int nb, int count, double2* C, const Done* done, hipStream_t st) {
+    if (done && nb * count <= 2 * kSmallSums && std::min(128, nb) * count <= kSmallSums) {
+        k_reduce_small<<<1, kSmallThreads, 0, st>>>(partial, nb, count, C, *done);
+        return;
+    }
+    k_reduce_partials<<<count, 256, 0, st>>>(partial, nb, count, C);
+    if (done) k_done<<<1, 64, 0, st>>>(*done);
+}
+
 hipError_t gram(const ColPtrs& L, int p, const ColPtrs& R, int q, long long N, double2* partial, int max_blocks,
-                double2* C, hipStream_t st) {
+                double2* C, hipStream_t st, const Done* done) {
     if (p <= 0 || q <= 0) return hipSuccess;
     // one wave per 16 columns of L
     const int TP = (p + 15) >> 4, TQ = (q + 15) >> 4;
@@ -762,7 +915,7 @@ hipError_t gram(const ColPtrs& L, int p, const ColPtrs& R, int q, long long N, d
         default: k_gram<4><<<nb, 64 * TP, 0, st>>>(L, p, R, q, N, gpb, partial); break;
     }
     int cnt = p * q;
-    k_reduce_partials<<<cnt, 256, 0, st>>>(partial, nb, cnt, C);
+    reduce_partials(partial, nb, cnt, C, done, st);
     return hipGetLastError();
 }
 
@@ -784,7 +937,7 @@ hipError_t lincomb(const ColPtrs& A, int p, const ColPtrs& Y, int q, const doubl
 }
 
 hipError_t gram_pairs(const ColPtrs& L, int p, const ColPtrs& R, int q, long long N, double2* partial, int max_blocks,
-                      double* C, hipStream_t st) {
+                      double* C, hipStream_t st, const Done* done) {
     if (p <= 0 || q <= 0) return hipSuccess;
     const int TP = (p + 15) >> 4, TQ = (q + 15) >> 4;
     long long gpb;
@@ -797,7 +950,23 @@ hipError_t gram_pairs(const ColPtrs& L, int p, const ColPtrs& R, int q, long lon
     }
     // 4pq real entries per block, reduced as 2pq pairs
     const int cnt = 2 * p * q;
-    k_reduce_partials<<<cnt, 256, 0, st>>>(partial, nb, cnt, reinterpret_cast<double2*>(C));
+    reduce_partials(partial, nb, cnt, reinterpret_cast<double2*>(C), done, st);
+    return hipGetLastError();
+}
+
+hipError_t lincomb_pairs_small(const SmallCols* A, int p, const SmallCols* Y, int q, int sets, const double* C,
+                               double beta, long long N, hipStream_t st) {
+    if (q <= 0) return hipSuccess;
+    if (p > kSmallP || q > kSmallP || 4 * p * q > kCoefArg) return hipErrorInvalidValue;
+    const dim3 nb((unsigned)std::min<long long>(4096, std::max<long long>(1, (N + 127) / 128)), sets);
+    CoefArg c;
+    std::copy(C, C + 4 * p * q, c.v);
+    const SmallCols &A1 = A[sets - 1], &Y1 = Y[sets - 1];
+    // the accumulators of lincomb_pairs' choice
+    const int qg = (q + 3) >> 2;
+    if (qg <= 2) k_lincomb_pairs_small<2><<<nb, 256, 0, st>>>(A[0], A1, p, Y[0], Y1, q, c, beta, N);
+    else if (qg <= 3) k_lincomb_pairs_small<3><<<nb, 256, 0, st>>>(A[0], A1, p, Y[0], Y1, q, c, beta, N);
+    else k_lincomb_pairs_small<4><<<nb, 256, 0, st>>>(A[0], A1, p, Y[0], Y1, q, c, beta, N);
     return hipGetLastError();
 }
 
@@ -818,12 +987,22 @@ hipError_t lincomb_pairs(const ColPtrs& A, int p, const ColPtrs& Y, int q, const
 }
 
 hipError_t residual_norm_pairs(const ColPtrs& HX, const ColPtrs& X, const ColPtrs& R, const Reals& theta, int m,
-                               long long N, double* partial, int max_blocks, double* out, hipStream_t st) {
+                               long long N, double* partial, int max_blocks, double* out, hipStream_t st,
+                               const Done* done) {
     if (m <= 0) return hipSuccess;
     if (2 * m > kMaxCols) return hipErrorInvalidValue;
     long long rpb = (N + max_blocks - 1) / max_blocks;
     int nb = (int)((N + rpb - 1) / rpb);
+    if (done && m <= kSmallCols && nb <= kSmallThreads && rpb <= 2) {
+        k_residual_small<<<1, kSmallThreads, 0, st>>>(HX, X, R, theta, m, (int)N, (int)rpb, out, *done);
+        return hipGetLastError();
+    }
     k_residual_norm_pairs<<<nb, 256, 0, st>>>(HX, X, R, theta, m, N, rpb, partial);
+    if (done) {
+        // the 2m sums of a block as m entries of two
+        reduce_partials(reinterpret_cast<const double2*>(partial), nb, m, reinterpret_cast<double2*>(out), done, st);
+        return hipGetLastError();
+    }
     k_reduce_real<<<2 * m, 256, 0, st>>>(partial, nb, 2 * m, out);
     return hipGetLastError();
 }
@@ -859,12 +1038,13 @@ hipError_t colnorm2(const ColPtrs& V, int m, long long N, double* partial, int m
 }
 
 hipError_t residual_norm(const ColPtrs& HX, const ColPtrs& X, const ColPtrs& R, const Reals& theta, int m, long long N,
-                         double* partial, int max_blocks, double* out, hipStream_t st) {
+                         double* partial, int max_blocks, double* out, hipStream_t st, const Done* done) {
     if (m <= 0) return hipSuccess;
     long long rpb = (N + max_blocks - 1) / max_blocks;
     int nb = (int)((N + rpb - 1) / rpb);
     k_residual_norm<<<nb, 256, 0, st>>>(HX, X, R, theta, m, N, rpb, partial);
     k_reduce_real<<<m, 256, 0, st>>>(partial, nb, m, out);
+    if (done) k_done<<<1, 64, 0, st>>>(*done);
     return hipGetLastError();
 }
 

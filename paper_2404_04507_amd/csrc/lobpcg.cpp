@@ -761,6 +761,8 @@ struct Solver {
     DeviceBuf dring;      // coefficient slots on the device
     double2* hsmall = nullptr;  // gram results and norms: pinned host memory the reductions write directly
     double2* hring = nullptr;   // pinned coefficient slots
+    unsigned* hflag = nullptr;  // pinned: number of the last small reduction that is done
+    unsigned seq = 0;           // number of the last one launched
     int ring_next = 0;
     int ring_since_sync = 0;
     int max_blocks = 1024;
@@ -774,6 +776,7 @@ static void solver_free(Solver* s) {
     dev_free(s->dring);
     if (s->hsmall) (void)hipHostFree(s->hsmall);
     if (s->hring) (void)hipHostFree(s->hring);
+    if (s->hflag) (void)hipHostFree(s->hflag);
     delete s;
 }
 
@@ -794,8 +797,12 @@ static int solver_ensure(iwfpm_plan_s* p, int m) {
     size_t need_small = (size_t)2 * 96 * 96 * sizeof(double2);
     size_t need_ring = (size_t)kRingSlots * kSlot * sizeof(double2);
     if (s->dring.bytes < need_ring && dev_alloc(s->dring, need_ring) != IWFPM_OK) return IWFPM_ERR_ALLOC;
-    if (!s->hsmall && hipHostMalloc((void**)&s->hsmall, need_small) != hipSuccess) return IWFPM_ERR_ALLOC;
+    if (!s->hsmall && hipHostMalloc((void**)&s->hsmall, need_small, hipHostMallocCoherent) != hipSuccess) return IWFPM_ERR_ALLOC;
     if (!s->hring && hipHostMalloc((void**)&s->hring, need_ring) != hipSuccess) return IWFPM_ERR_ALLOC;
+    if (!s->hflag) {
+        if (hipHostMalloc((void**)&s->hflag, 64, hipHostMallocCoherent) != hipSuccess) return IWFPM_ERR_ALLOC;
+        *s->hflag = s->seq;
+    }
     return IWFPM_OK;
 }
 
@@ -851,6 +858,24 @@ static int sync(Ctx& c) {
     return IWFPM_OK;
 }
 
+// Wait for the small reduction numbered s->seq: its results, and everything
+// before it on the stream, are there when the flag shows it.  The wait spins
+// for a bounded time and then falls back on the stream, which also reports
+// errors.
+static int wait_done(Ctx& c) {
+    Solver* s = c.s;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int k = 1; __atomic_load_n(s->hflag, __ATOMIC_ACQUIRE) != s->seq; ++k) {
+        if (k % 1024) continue;
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) continue;
+        if (int rc = sync(c)) return rc;
+        if (__atomic_load_n(s->hflag, __ATOMIC_ACQUIRE) != s->seq) return IWFPM_ERR_DEVICE;
+    }
+    s->ring_since_sync = 0;
+    return IWFPM_OK;
+}
+static Done next_done(Ctx& c) { return Done{c.s->hflag, ++c.s->seq}; }
+
 // C (p x q) = L^H R on the host, chunking both sides by kMaxCols
 static int host_gram(Ctx& c, const std::vector<double2*>& L, const std::vector<double2*>& R, std::vector<cd>& C) {
     const int p = (int)L.size(), q = (int)R.size();
@@ -865,8 +890,9 @@ static int host_gram(Ctx& c, const std::vector<double2*>& L, const std::vector<d
             ColPtrs a{}, b{};
             for (int i = 0; i < pi; ++i) a.p[i] = L[i0 + i];
             for (int j = 0; j < qj; ++j) b.p[j] = R[j0 + j];
-            CHECK_HIP(gram(a, pi, b, qj, c.N, (double2*)c.s->partial.ptr, c.s->max_blocks, h, c.st));
-            if (int rc = sync(c)) return rc;
+            const Done done = next_done(c);
+            CHECK_HIP(gram(a, pi, b, qj, c.N, (double2*)c.s->partial.ptr, c.s->max_blocks, h, c.st, &done));
+            if (int rc = wait_done(c)) return rc;
             for (int j = 0; j < qj; ++j)
                 for (int i = 0; i < pi; ++i) {
                     double2 v = h[(size_t)j * pi + i];
@@ -1185,8 +1211,9 @@ static int host_gram_real(Ctx& c, const std::vector<RVec>& L, const std::vector<
             ColPtrs a{}, b{};
             for (int i = 0; i < pi; ++i) a.p[i] = Lp.cols[i0 + i];
             for (int j = 0; j < qj; ++j) b.p[j] = Rp.cols[j0 + j];
-            CHECK_HIP(gram_pairs(a, pi, b, qj, c.N, (double2*)c.s->partial.ptr, c.s->max_blocks, h, c.st));
-            if (int rc = sync(c)) return rc;
+            const Done done = next_done(c);
+            CHECK_HIP(gram_pairs(a, pi, b, qj, c.N, (double2*)c.s->partial.ptr, c.s->max_blocks, h, c.st, &done));
+            if (int rc = wait_done(c)) return rc;
             for (int s2 = 0; s2 < 2 * qj; ++s2)
                 for (int r2 = 0; r2 < 2 * pi; ++r2)
                     Gf[(size_t)(2 * i0 + r2) + (size_t)(2 * j0 + s2) * ldf] = h[(size_t)r2 + (size_t)s2 * 2 * pi];
@@ -1196,6 +1223,49 @@ static int host_gram_real(Ctx& c, const std::vector<RVec>& L, const std::vector<
     G.assign((size_t)nl * nr, 0.0);
     for (int l = 0; l < nr; ++l)
         for (int k = 0; k < nl; ++k) G[k + (size_t)l * nl] = Gf[(size_t)Lp.at[k] + (size_t)Rp.at[l] * ldf];
+    return IWFPM_OK;
+}
+
+// One combination, or two with the same coefficients over vectors that lie alike
+// in buffers of their own, as one launch that carries the coefficients; *taken:
+// how many of the n were done (0 where they do not fit a launch)
+struct RealLin {
+    const std::vector<RVec> *A, *Y;
+};
+static int dev_lincomb_real_small(Ctx& c, const RealLin* sets, int n, const std::vector<cd>& Cm, int ldc, double beta,
+                                  int* taken) {
+    *taken = 0;
+    // two vectors to a column at most: the layouts of larger ones need no look
+    if (sets[0].A->size() > 2 * kSmallP || sets[0].Y->size() > 2 * kSmallP ||
+        sets[0].A->size() * sets[0].Y->size() > kCoefArg)
+        return IWFPM_OK;
+    PairCols A[2], Y[2];
+    for (int k = 0; k < n; ++k) {
+        A[k] = pair_cols(*sets[k].A);
+        Y[k] = pair_cols(*sets[k].Y);
+    }
+    const int P = (int)A[0].cols.size(), Q = (int)Y[0].cols.size();
+    if (P == 0 || Q == 0 || P > kSmallP || Q > kSmallP || 4 * P * Q > kCoefArg) return IWFPM_OK;
+    if (n == 2) {
+        const auto meet = [](const PairCols& u, const PairCols& v) {
+            for (double2* x : u.cols)
+                if (std::find(v.cols.begin(), v.cols.end(), x) != v.cols.end()) return true;
+            return false;
+        };
+        if (A[0].at != A[1].at || Y[0].at != Y[1].at || meet(Y[0], Y[1]) || meet(Y[0], A[1]) || meet(A[0], Y[1])) n = 1;
+    }
+    double h[kCoefArg];
+    std::fill(h, h + 4 * P * Q, 0.0);
+    for (size_t i = 0; i < A[0].at.size(); ++i)
+        for (size_t l = 0; l < Y[0].at.size(); ++l)
+            h[(size_t)A[0].at[i] + (size_t)Y[0].at[l] * 2 * P] = Cm[i + l * (size_t)ldc].real();
+    SmallCols a[2], y[2];
+    for (int k = 0; k < n; ++k) {
+        std::copy(A[k].cols.begin(), A[k].cols.end(), a[k].p);
+        std::copy(Y[k].cols.begin(), Y[k].cols.end(), y[k].p);
+    }
+    CHECK_HIP(lincomb_pairs_small(a, P, y, Q, n, h, beta, c.N, c.st));
+    *taken = n;
     return IWFPM_OK;
 }
 
@@ -1692,10 +1762,22 @@ static int tall_grams(Tall& t, const std::vector<GramQ<Rt>>& q, std::vector<std:
 template <class Rt>
 static int tall_lincombs(Tall& t, const std::vector<LinQ<Rt>>& q) {
     if (t.single) {
-        for (const auto& x : q) {
+        for (size_t k = 0; k < q.size(); ++k) {
+            const auto& x = q[k];
             int rc;
-            if constexpr (Rt::real) rc = dev_lincomb_real(*x.c, x.A, x.Y, *x.C, x.ldc, 0, x.beta);
-            else rc = dev_lincomb(*x.c, x.A, x.Y, *x.C, x.ldc, 0, x.beta);
+            if constexpr (Rt::real) {
+                // requests come in pairs: vectors, then their images under H~
+                const LinQ<Rt>& z = q[std::min(k + 1, q.size() - 1)];
+                const bool two = k + 1 < q.size() && z.c == x.c && z.C == x.C && z.ldc == x.ldc && z.beta == x.beta;
+                const RealLin sets[2] = {{&x.A, &x.Y}, {&z.A, &z.Y}};
+                int taken = 0;
+                if ((rc = dev_lincomb_real_small(*x.c, sets, two ? 2 : 1, *x.C, x.ldc, x.beta, &taken))) return rc;
+                if (taken) {
+                    k += taken - 1;
+                    continue;
+                }
+                rc = dev_lincomb_real(*x.c, x.A, x.Y, *x.C, x.ldc, 0, x.beta);
+            } else rc = dev_lincomb(*x.c, x.A, x.Y, *x.C, x.ldc, 0, x.beta);
             if (rc) return rc;
         }
         return IWFPM_OK;
@@ -1731,13 +1813,14 @@ static int tall_residuals(Tall& t, std::vector<BInst>& in, const std::vector<int
             for (int v = 0; v < per; ++v) th.v[v] = v < m ? b.theta[v] : 0.0;
             // the norms land in the pinned host mirror directly
             double* h = (double*)(b.s->hsmall + 96 * 96);
+            const Done done = next_done(b.c);
             if constexpr (Rt::real)
                 CHECK_HIP(residual_norm_pairs(hx, x, r, th, mc, b.c.N, (double*)b.s->partial.ptr, b.s->max_blocks, h,
-                                              b.c.st));
+                                              b.c.st, &done));
             else
                 CHECK_HIP(residual_norm(hx, x, r, th, m, b.c.N, (double*)b.s->partial.ptr, b.s->max_blocks, h,
-                                        b.c.st));
-            if (int rc = sync(b.c)) return rc;
+                                        b.c.st, &done));
+            if (int rc = wait_done(b.c)) return rc;
             std::copy(h, h + per, nrm.begin() + (size_t)k * per);
         }
     } else {
