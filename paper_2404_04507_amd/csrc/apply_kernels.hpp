@@ -173,8 +173,8 @@ __device__ __forceinline__ int long_axis_perm(const DevGeom& g, int ax, int c) {
     int l = 0, mult = 1, B = g.ext[ax];
     for (int i = 0; i < g.nfac[ax]; ++i) {
         const int f = g.fac[ax][i];
-        const int st = B / f;
-        const int k = c / st;
+        const int st = (unsigned)B / (unsigned)f;
+        const int k = (unsigned)c / (unsigned)st;
         c -= k * st;
         l += mult * k;
         mult *= f;
@@ -188,7 +188,7 @@ __device__ __forceinline__ int unperm_pos(const DevGeom& g, int pos) {
     int out = pos;
     for (int ax = 0; ax < g.n; ++ax) {
         if (g.nfac[ax] <= 1) continue;
-        const int c = (pos / g.stride[ax]) % g.ext[ax];
+        const int c = (unsigned)pos / (unsigned)g.stride[ax] % (unsigned)g.ext[ax];
         out += (long_axis_perm(g, ax, c) - c) * g.stride[ax];
     }
     return out;
@@ -212,6 +212,13 @@ __device__ __forceinline__ void run_axis(cplx<R>* lds, int S, int npencil, int e
 // between the two): entry k of the pencil with offset r = (p mod es) / es_tw
 // in its block is multiplied by tw[r k mult] (conjugated for SIGN < 0).  A
 // loop of its own, so that run_axis keeps the bare pencil loop.
+//
+// Twiddles and entries are read kTwBatch at a time: one by one each waited for
+// a load from the table (a 12-point stage of a 120-point axis 4500 -> 3400
+// cycles).  The products' roundings are spelled out, so that no unrolling
+// changes them.
+constexpr int kTwBatch = 4;
+
 template <int SIGN, typename R>
 __device__ __forceinline__ void twiddle_axis(cplx<R>* lds, int S, int npencil, int es, RowGeom rg,
                                              const cplx<R>* __restrict__ tw, int es_tw, int mult) {
@@ -222,11 +229,22 @@ __device__ __forceinline__ void twiddle_axis(cplx<R>* lds, int S, int npencil, i
         const int tstep = dtw.div(lo) * mult;
         if (!tstep) continue;
         cplx<R>* base = lds + phys(hi * es * S + lo, rg, dsl);
-        for (int k = 1; k < S; ++k) {
-            const cplx<R> w = tw[k * tstep];
-            cplx<R>& v = base[k * pes];
-            if (SIGN > 0) v = cplx<R>{v.x * w.x - v.y * w.y, v.x * w.y + v.y * w.x};
-            else v = cplx<R>{v.x * w.x + v.y * w.y, v.y * w.x - v.x * w.y};
+        for (int k0 = 1; k0 < S; k0 += kTwBatch) {
+            cplx<R> w[kTwBatch], v[kTwBatch];
+#pragma unroll
+            for (int u = 0; u < kTwBatch; ++u) {
+                const int k = min(k0 + u, S - 1);
+                w[u] = tw[k * tstep];
+                v[u] = base[k * pes];
+            }
+#pragma unroll
+            for (int u = 0; u < kTwBatch; ++u) {
+                const cplx<R> a = v[u], b = w[u];
+                cplx<R> r;
+                if (SIGN > 0) r = {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+                else r = {fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -(a.x * b.y))};
+                if (k0 + u < S) base[(k0 + u) * pes] = r;
+            }
         }
     }
 }
@@ -249,11 +267,13 @@ __device__ __forceinline__ void run_axis_any(const DevGeom& g, const DevTabs& t,
         if (m > 1) {
             const int i = SIGN > 0 ? st : m - 1 - st;
             int B = S;
-            for (int j = 0; j < i; ++j) B /= g.fac[ax][j];
+            mult = 1;
+            for (int j = 0; j < i; ++j) mult *= g.fac[ax][j];
             f = g.fac[ax][i];
-            np = npencil * (S / f);
-            esf = (B / f) * es;
-            mult = S / B;
+            const Div16 df(f);
+            B = Div16(mult).div(S);
+            np = npencil * df.div(S);
+            esf = df.div(B) * es;
             if (i < m - 1) tw = tw_of<R>(t, g, ax);
         }
         if (SIGN < 0 && tw) twiddle_axis<SIGN, R>(lds, f, np, esf, rg, tw, es, mult);
@@ -266,11 +286,6 @@ __device__ __forceinline__ void run_axis_any(const DevGeom& g, const DevTabs& t,
 // ---------------------------------------------------------------------------
 // index maps (Sec. 3.2)
 // ---------------------------------------------------------------------------
-
-__device__ __forceinline__ int pmod(int a, int m) {
-    int r = a % m;
-    return r < 0 ? r + m : r;
-}
 
 // Per-row data of the kinetic term and of the window order, for the row whose
 // first element sits at grid position r0 (a multiple of the last extent):
@@ -300,19 +315,21 @@ __device__ __forceinline__ RowTable row_table_at(unsigned char* base, int rows, 
 
 __device__ __forceinline__ void row_entry(const DevGeom& g, const DevTabs& t, int r0, RowTable tab, int row) {
     const int d = g.d, n = g.n;
-    const int s = r0 / g.nkI;
-    int q = r0 - s * g.nkI;
+    const int s = (unsigned)r0 / (unsigned)g.nkI;
+    unsigned q = r0 - s * g.nkI;
     const int* a = t.slice_a + s * d;
+    const int* am = t.slice_m + s * d;
     const double* gg = t.slice_g + s * d;
     double kI[kMaxAxes];
     int vrow = s * g.nkI;
-    q /= g.ext[n - 1];  // the row starts at column 0 of the last axis
+    q /= (unsigned)g.ext[n - 1];  // the row starts at column 0 of the last axis
     for (int j = d - 2; j >= 0; --j) {
         int ax = n - d + j;
-        int E = g.ext[ax];
-        int ks = q % E;
-        q /= E;
-        int pj = pmod(ks - a[j], E);
+        const unsigned E = g.ext[ax], h = q / E;
+        int ks = q - h * E;
+        q = h;
+        int pj = ks - am[j];
+        pj += pj < 0 ? (int)E : 0;
         kI[j] = (double)(a[j] + pj);
         vrow += (g.order ? pj : ks) * g.stride[ax];
     }
@@ -321,39 +338,43 @@ __device__ __forceinline__ void row_entry(const DevGeom& g, const DevTabs& t, in
         for (int i = 0; i < d - 1; ++i) b += g.P1[j * d + i] * kI[i];
         tab.B[row * d + j] = b;
     }
-    const int El = g.ext[n - 1];
     tab.alast[row] = a[d - 1];
-    tab.amod[row] = pmod(a[d - 1], El);
+    tab.amod[row] = am[d - 1];
     tab.vrow[row] = vrow;
 }
 
-// kinetic term and vector position of column c of a row (see RowTable)
-__device__ __forceinline__ double row_kinetic(const DevGeom& g, const RowTable& tab, int row, int c, int* vpos) {
-    const int d = g.d;
-    const int El = g.ext[g.n - 1];
+// kinetic term and vector position of column c of a row (see RowTable); D: the
+// number of k_I axes where it is compiled in, else 0, and P: the last column of
+// P1 then
+template <int D>
+__device__ __forceinline__ double row_kinetic(const DevGeom& g, const double* P, const RowTable& tab, int row, int c,
+                                              int El, int order, int* vpos) {
+    const int d = D > 0 ? D : g.d;
     int pl = c - tab.amod[row];
     pl += pl < 0 ? El : 0;
     const double kl = (double)(tab.alast[row] + pl);
     double lam = 0.0;
+#pragma unroll
     for (int j = 0; j < d; ++j) {
-        double v = tab.B[row * d + j] + g.P1[j * d + d - 1] * kl;
-        lam += v * v;
+        const double v = fma(D > 0 ? P[j] : g.P1[j * d + d - 1], kl, tab.B[row * d + j]);
+        lam = fma(v, v, lam);
     }
-    *vpos = tab.vrow[row] + (g.order ? pl : c);
+    *vpos = tab.vrow[row] + (order ? pl : c);
     return 0.5 * lam;
 }
 
 // window-order position r (within one vector) -> grid-order position
-__device__ __forceinline__ int vec_to_grid(const DevGeom& g, const int* __restrict__ slice_a, int r) {
-    int s = r / g.nkI;
-    int q = r - s * g.nkI;
+__device__ __forceinline__ int vec_to_grid(const DevGeom& g, const int* __restrict__ slice_m, int r) {
+    const int s = (unsigned)r / (unsigned)g.nkI;
+    unsigned q = r - s * g.nkI;
     int out = s * g.nkI;
     for (int j = g.d - 1; j >= 0; --j) {
         int ax = g.n - g.d + j;
-        int E = g.ext[ax];
-        int pj = q % E;
-        q /= E;
-        out += pmod(pj + slice_a[s * g.d + j], E) * g.stride[ax];
+        const unsigned E = g.ext[ax], h = q / E;
+        unsigned pj = q - h * E + slice_m[s * g.d + j];
+        q = h;
+        pj -= pj >= E ? E : 0;
+        out += (int)pj * g.stride[ax];
     }
     return out;
 }
@@ -377,7 +398,7 @@ __device__ __forceinline__ R vsum_except(const DevGeom& g, const R* __restrict__
     R acc = R(0);
     for (int ax = 0; ax < g.n; ++ax) {
         if (ax == skip) continue;
-        int l = (r / g.stride[ax]) % g.ext[ax];
+        const int l = (unsigned)r / (unsigned)g.stride[ax] % (unsigned)g.ext[ax];
         acc += vtab[g.voff[ax] + l];
     }
     return acc;
@@ -434,9 +455,10 @@ struct alignas(16) CPair {
 struct RowIter {
     int e, row, col, drow, dcol, sl;
     __device__ __forceinline__ RowIter(int start, int step, int sl_) : e(start), sl(sl_) {
-        row = start / sl_;
+        const Div16 d(sl_);
+        row = d.div(start);
         col = start - row * sl_;
-        drow = step / sl_;
+        drow = d.div(step);
         dcol = step - drow * sl_;
     }
     __device__ __forceinline__ void next(int step) {
@@ -458,10 +480,11 @@ __device__ __forceinline__ void load_gather(const DevGeom& g, const DevTabs& t, 
     const int nt = blockDim.x;
     if (g.order) {
         // rowmap[rv] = (grid row within the tile) * sp, and the rotation of the last axis
-        const int rows = count / rg.sl;
+        const Div16 dsl(rg.sl);
+        const int rows = dsl.div(count);
         for (int rv = threadIdx.x; rv < rows; rv += nt) {
-            int gp = vec_to_grid(g, t.slice_a, v0 + rv * rg.sl);  // element 0 of this vector row
-            int grow = (gp - v0) / rg.sl;
+            int gp = vec_to_grid(g, t.slice_m, v0 + rv * rg.sl);  // element 0 of this vector row
+            int grow = dsl.div(gp - v0);
             rowmap[2 * rv] = grow * rg.sp;
             rowmap[2 * rv + 1] = gp - v0 - grow * rg.sl;  // its column = a_last mod sl
         }
@@ -471,7 +494,7 @@ __device__ __forceinline__ void load_gather(const DevGeom& g, const DevTabs& t, 
             RowIter j = it;
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                v[u] = j.e < count ? x[v0 + j.e] : make_double2(0.0, 0.0);
+                v[u] = x[v0 + min(j.e, count - 1)];
                 j.next(nt);
             }
 #pragma unroll
@@ -490,7 +513,7 @@ __device__ __forceinline__ void load_gather(const DevGeom& g, const DevTabs& t, 
             RowIter j = it;
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                v[u] = j.e < count ? x[v0 + j.e] : make_double2(0.0, 0.0);
+                v[u] = x[v0 + min(j.e, count - 1)];
                 j.next(nt);
             }
 #pragma unroll
@@ -535,7 +558,7 @@ __device__ __forceinline__ void load_tile(const cplx<R>* __restrict__ w, int cou
                 RowIter j = it;
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
-                    v[u] = j.e < count2 ? __builtin_nontemporal_load(w4 + j.e) : nt_f4{0.f, 0.f, 0.f, 0.f};
+                    v[u] = __builtin_nontemporal_load(w4 + min(j.e, count2 - 1));
                     j.next(nt);
                 }
 #pragma unroll
@@ -556,7 +579,7 @@ __device__ __forceinline__ void load_tile(const cplx<R>* __restrict__ w, int cou
         RowIter j = it;
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            v[u] = j.e < count ? nt_load(&w[j.e]) : cplx<R>{R(0), R(0)};
+            v[u] = nt_load(&w[min(j.e, count - 1)]);
             j.next(nt);
         }
 #pragma unroll
@@ -584,38 +607,68 @@ __device__ __forceinline__ void store_tile(cplx<R>* __restrict__ w, int count, c
     for (RowIter it(threadIdx.x, nt, rg.sl); it.e < count; it.next(nt)) w[it.e] = tile[it.row * rg.sp + it.col];
 }
 
+// Lambda x + tile -> y for the rows in the table, NB elements of a thread in
+// flight.  Small grids are bound by the latency of each step, so what all
+// elements share is read before the loop, and an element past the end reads
+// the first one's place: nothing in a batch waits on a branch or on a scalar
+// load, as the loop over d axes did for every element (the scatter of 1200
+// points by 128 threads 9200 -> 6700 cycles of 40,000; the whole apply of 576 to
+// 600,000 points 3 to 15 % less time).  NB = 8 where a workgroup is alone with
+// its vector; 4 in pass 3, whose registers 8 raised from 106 to 148 (float32:
+// 52.9 -> 59.1 us on 884,736 points, 51.2 with 4).
+template <int D, int NB, typename R>
+__device__ __forceinline__ void kinetic_rows(const DevGeom& g, const double2* __restrict__ x, double2* __restrict__ y,
+                                             int count, const cplx<R>* tile, RowGeom rg, const RowTable& tab) {
+    const int nt = blockDim.x, El = g.ext[g.n - 1], order = g.order;
+    const bool kin = g.kin != 0;
+    double P[D > 0 ? D : 1];
+#pragma unroll
+    for (int j = 0; j < D; ++j) P[j] = g.P1[j * D + D - 1];
+    for (RowIter it(threadIdx.x, nt, rg.sl); it.e < count;) {
+        int vpos[NB];
+        double lam[NB];
+        double2 xv[NB];
+        cplx<R> c[NB];
+        RowIter j = it;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int row = j.e < count ? j.row : 0, col = j.e < count ? j.col : 0;
+            lam[u] = row_kinetic<D>(g, P, tab, row, col, El, order, &vpos[u]);
+            c[u] = tile[row * rg.sp + col];
+            j.next(nt);
+        }
+        if (kin) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) xv[u] = x[vpos[u]];
+        } else {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) xv[u] = make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+            if (it.e + u * nt < count)
+                __builtin_nontemporal_store(
+                    nt_d2{fma(lam[u], xv[u].x, (double)c[u].x), fma(lam[u], xv[u].y, (double)c[u].y)},
+                    reinterpret_cast<nt_d2*>(y + vpos[u]));
+        it = j;
+    }
+}
+
 // kinetic term + scatter for `count` grid-order elements starting at grid
 // position r0 of one vector: y[v] = Lambda x[v] + tile
-template <typename R>
+template <int NB, typename R>
 __device__ __forceinline__ void kinetic_scatter(const DevGeom& g, const DevTabs& t, const double2* __restrict__ x,
                                                 double2* __restrict__ y, int r0, int count, const cplx<R>* tile,
                                                 RowGeom rg, RowTable tab) {
     const int nt = blockDim.x;
-    const int rows = count / rg.sl;
+    const int rows = Div16(rg.sl).div(count);
     for (int r = threadIdx.x; r < rows; r += nt) row_entry(g, t, r0 + r * rg.sl, tab, r);
     __syncthreads();
-    for (RowIter it(threadIdx.x, nt, rg.sl); it.e < count;) {
-        int vpos[kBatch];
-        double lam[kBatch];
-        double2 xv[kBatch];
-        RowIter j = it;
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            if (j.e < count) {
-                lam[u] = row_kinetic(g, tab, j.row, j.col, &vpos[u]);
-                xv[u] = g.kin ? x[vpos[u]] : make_double2(0.0, 0.0);
-            }
-            j.next(nt);
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            if (it.e < count) {
-                cplx<R> c = tile[it.row * rg.sp + it.col];
-                __builtin_nontemporal_store(nt_d2{lam[u] * xv[u].x + (double)c.x, lam[u] * xv[u].y + (double)c.y},
-                                            reinterpret_cast<nt_d2*>(y + vpos[u]));
-            }
-            it.next(nt);
-        }
+    switch (g.d) {
+        case 1: kinetic_rows<1, NB, R>(g, x, y, count, tile, rg, tab); break;
+        case 2: kinetic_rows<2, NB, R>(g, x, y, count, tile, rg, tab); break;
+        case 3: kinetic_rows<3, NB, R>(g, x, y, count, tile, rg, tab); break;
+        default: kinetic_rows<0, NB, R>(g, x, y, count, tile, rg, tab); break;
     }
 }
 
@@ -663,7 +716,7 @@ __device__ __forceinline__ void fused_body(const DevGeom& g, const DevTabs& t, R
         run_axis_any<-1, R, MAXS>(g, t, ax, tile, N / g.ext[ax], g.stride[ax], rg);
         __syncthreads();
     }
-    kinetic_scatter<R>(g, t, x, y, 0, N, tile, rg, row_table_at(extra, rows, g.d));
+    kinetic_scatter<kBatch, R>(g, t, x, y, 0, N, tile, rg, row_table_at(extra, rows, g.d));
 }
 
 template <typename R, int MAXS>
@@ -831,7 +884,7 @@ __device__ __forceinline__ R p2_row_sum(const DevGeom& g, const R* vt, int split
     const int o = e * g.ext[split - 1];
     R acc = R(0);
     for (int a = 0; a < split - 1; ++a) {
-        int c = (o / (g.stride[a] / sin_)) % g.ext[a];
+        int c = (unsigned)o / ((unsigned)g.stride[a] / (unsigned)sin_) % (unsigned)g.ext[a];
         if (g.nfac[a] > 1) c = long_axis_perm(g, a, c);
         acc += vt[g.voff[a] + c];
     }
@@ -841,7 +894,7 @@ template <typename R>
 __device__ __forceinline__ R p2_col_sum(const DevGeom& g, const R* vt, int split, int cc) {
     R acc = R(0);
     for (int a = split; a < g.n; ++a) {
-        int c = (cc / g.stride[a]) % g.ext[a];
+        int c = (unsigned)cc / (unsigned)g.stride[a] % (unsigned)g.ext[a];
         if (g.nfac[a] > 1) c = long_axis_perm(g, a, c);
         acc += vt[g.voff[a] + c];
     }
@@ -1140,7 +1193,7 @@ __device__ __forceinline__ void pass3_body(const DevGeom& g, const DevTabs& t, c
         run_axis_any<-1, R, MAXS>(g, t, ax, tile, count / g.ext[ax], g.stride[ax], rg);
         __syncthreads();
     }
-    kinetic_scatter<R>(g, t, psi + off, hpsi + off, r0, count, tile, rg,
+    kinetic_scatter<kBatch / 2, R>(g, t, psi + off, hpsi + off, r0, count, tile, rg,
                        row_table_at(extra, G * sin_ / rg.sl, g.d));
 }
 
