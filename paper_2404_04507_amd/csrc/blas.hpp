@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 
 namespace iwfpm {
 
@@ -26,6 +27,20 @@ struct Done {
     unsigned* flag;
     unsigned seq;
 };
+
+// Wait until done's flag is raised: its results, and everything before it on the
+// stream, are there then.  The wait spins for a bounded time and then falls back
+// on the stream, which also reports errors.
+inline hipError_t wait_done(const Done& done, hipStream_t st) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int k = 1; __atomic_load_n(done.flag, __ATOMIC_ACQUIRE) != done.seq; ++k) {
+        if (k % 1024 || std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) continue;
+        const hipError_t e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return e;
+        return __atomic_load_n(done.flag, __ATOMIC_ACQUIRE) == done.seq ? hipSuccess : hipErrorUnknown;
+    }
+    return hipSuccess;
+}
 
 // C (p x q, column-major, C[j*p + i]) = L^H R; `partial` holds max_blocks*p*q entries.
 // done (here and below): raise its flag when C is written

@@ -58,6 +58,8 @@ struct LearnedPrecond {
     DeviceBuf work;   // wblocks blocks of wcols columns
     DeviceBuf small, partial;  // coefficients of combinations, Gram partial sums (training)
     double2* h_small = nullptr;  // pinned: Gram results (the reduction writes them here), then kCoefSlots coefficient slots
+    unsigned* flag = nullptr;    // pinned, behind them: number of the last Gram that is done
+    unsigned seq = 0;            // number of the last one launched
     int wcols = 0, wblocks = 0;
     long long version = 0;
 };
@@ -281,8 +283,9 @@ constexpr size_t kGramOut = (size_t)kMaxCols * kMaxCols, kCoef = (size_t)kMaxCol
 
 // out (p x q, column-major) = L^H R: the reduction writes the pinned mirror
 static int dgram(LearnedPrecond* lp, const ColPtrs& L, int p, const ColPtrs& R, int q, cvec& out, hipStream_t st) {
-    if (gram(L, p, R, q, lp->N, (double2*)lp->partial.ptr, kGramBlocks, lp->h_small, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
+    const Done done{lp->flag, ++lp->seq};
+    if (gram(L, p, R, q, lp->N, (double2*)lp->partial.ptr, kGramBlocks, lp->h_small, st, &done) != hipSuccess ||
+        wait_done(done, st) != hipSuccess)
         return IWFPM_ERR_DEVICE;
     out.resize((size_t)p * q);
     for (size_t e = 0; e < out.size(); ++e) out[e] = {lp->h_small[e].x, lp->h_small[e].y};
@@ -427,10 +430,14 @@ static int lp_rr_loss_grad(LearnedPrecond* lp, const double2* X, int m, const do
     int rc = lp_ensure_work(lp, m, WB_COUNT);
     if (rc) return rc;
     if (!lp->small.ptr && dev_alloc(lp->small, kCoefSlots * kCoef * sizeof(double2))) return IWFPM_ERR_ALLOC;
-    if (!lp->h_small &&
-        hipHostMalloc((void**)&lp->h_small, (kGramOut + kCoefSlots * kCoef) * sizeof(double2)) != hipSuccess) {
-        lp->h_small = nullptr;
-        return IWFPM_ERR_ALLOC;
+    if (!lp->h_small) {
+        const size_t entries = kGramOut + kCoefSlots * kCoef;
+        if (hipHostMalloc((void**)&lp->h_small, (entries + 1) * sizeof(double2), hipHostMallocCoherent) != hipSuccess) {
+            lp->h_small = nullptr;
+            return IWFPM_ERR_ALLOC;
+        }
+        lp->flag = (unsigned*)(lp->h_small + entries);
+        *lp->flag = lp->seq;
     }
     if (!lp->partial.ptr && dev_alloc(lp->partial, (size_t)kGramBlocks * kMaxCols * kMaxCols * sizeof(double2)))
         return IWFPM_ERR_ALLOC;

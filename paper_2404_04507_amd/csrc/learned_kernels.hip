@@ -367,6 +367,7 @@ __global__ void k_scale(const double2* __restrict__ A, double2* __restrict__ Y, 
                         long long N) {
     for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < N; k += (long long)gridDim.x * blockDim.x) {
         double s = d[k];
+#pragma unroll 4
         for (int j = 0; j < m; ++j) {
             double2 a = A[(size_t)j * N + k];
             Y[(size_t)j * N + k] = make_double2(s * a.x, s * a.y);
@@ -429,6 +430,7 @@ __global__ void __launch_bounds__(256) k_shell_grad(const double2* __restrict__ 
     double gb0 = 0.0, gb1 = 0.0, gbd = 0.0;
     for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < N; k += (long long)gridDim.x * blockDim.x) {
         double dd = 0.0, de = 0.0, ga = 0.0, gc = 0.0;
+#pragma unroll 4
         for (int j = 0; j < m; ++j) {
             const size_t o = (size_t)j * N + k;
             double2 g = G[o], r = R[o], a = A[o], c = C[o], p1 = B1[o], p2 = B2[o];

@@ -761,7 +761,7 @@ struct Solver {
     DeviceBuf dring;      // coefficient slots on the device
     double2* hsmall = nullptr;  // gram results and norms: pinned host memory the reductions write directly
     double2* hring = nullptr;   // pinned coefficient slots
-    unsigned* hflag = nullptr;  // pinned: number of the last small reduction that is done
+    unsigned* hflag = nullptr;  // pinned: number of the last reduction that is done
     unsigned seq = 0;           // number of the last one launched
     int ring_next = 0;
     int ring_since_sync = 0;
@@ -858,20 +858,10 @@ static int sync(Ctx& c) {
     return IWFPM_OK;
 }
 
-// Wait for the small reduction numbered s->seq: its results, and everything
-// before it on the stream, are there when the flag shows it.  The wait spins
-// for a bounded time and then falls back on the stream, which also reports
-// errors.
+// wait for the reduction numbered s->seq
 static int wait_done(Ctx& c) {
-    Solver* s = c.s;
-    const auto t0 = std::chrono::steady_clock::now();
-    for (int k = 1; __atomic_load_n(s->hflag, __ATOMIC_ACQUIRE) != s->seq; ++k) {
-        if (k % 1024) continue;
-        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) continue;
-        if (int rc = sync(c)) return rc;
-        if (__atomic_load_n(s->hflag, __ATOMIC_ACQUIRE) != s->seq) return IWFPM_ERR_DEVICE;
-    }
-    s->ring_since_sync = 0;
+    if (wait_done(Done{c.s->hflag, c.s->seq}, c.st) != hipSuccess) return IWFPM_ERR_DEVICE;
+    c.s->ring_since_sync = 0;
     return IWFPM_OK;
 }
 static Done next_done(Ctx& c) { return Done{c.s->hflag, ++c.s->seq}; }
