@@ -230,7 +230,19 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
     for (size_t k = 0; k < b->few.size(); ++k) {
         int* s = start + k * (b->B + 1);
         s[0] = 0;
-        for (int i = 0; i < b->B; ++i) s[i + 1] = s[i] + (few[i].kind == b->few[k].kind ? few_blocks(few[i], few_points) : 0);
+        // A star item deals its groups (the steps of one vector) to the XCDs from
+        // the first on, and the next item goes on where it ended: all from the
+        // first left the last XCDs idle (eight windows, ragged: 181 -> 146 us; 8
+        // plans of 24^2 x 32^2 points, one vector each: 93 -> 54 us)
+        int rot = 0;
+        for (int i = 0; i < b->B; ++i) {
+            FewItem& f = few[i];
+            s[i + 1] = s[i];
+            if (f.kind != b->few[k].kind) continue;
+            s[i + 1] += few_blocks(f, few_points);
+            f.rot = (8 - rot) & 7;
+            rot = (rot + f.w.chunks * f.nvec) & 7;
+        }
     }
     head->B = b->B;
     for (int k = 0; k < 3; ++k) head->total[k] = tot[k];

@@ -87,6 +87,7 @@ struct FewItem {
     double2* hpsi;
     int nvec;
     int kind;        // few_kind, -1: not a few-mode plan
+    int rot;         // star: XCDs that its groups of workgroups are turned by
     int gx, vb;      // point kernel: workgroups per group of vectors, vectors of a group
 };
 struct FewLaunch {
