@@ -567,9 +567,8 @@ def run_eigenfunction(lib, W, reps=5):
     """The ground state in physical space (eq:int) on the paper's 2D
     observation grid [-50, 50]^2, step 0.1 (1001 x 1001 points): the paper's
     Ex. 4.2 case I window (K = 6, L = 20) and the 2D/4D benchmark window.
-    Algorithmic flops = 8 N x points (one complex multiply-add per window
-    point and grid point); median of `reps` timed calls with the frequencies
-    and scratch already set up."""
+    flops: those of the two sums, 8 per complex multiply-add; median of `reps`
+    timed calls with the frequencies and scratch already set up."""
     import math
     import torch
     cases = [("ex4.2 case I K=6 L=20", W.paper_example_2d(0.8 * math.pi, 0.2 * math.pi, 6, 20), "fp64"),
@@ -590,7 +589,9 @@ def run_eigenfunction(lib, W, reps=5):
                 torch.cuda.synchronize()
                 ts.append(e0.elapsed_time(e1))
             ms = sorted(ts)[len(ts) // 2]
-            flops = 8.0 * plan.N * npts[0] * npts[1]
+            # the sums over the last k_I axis first (P_I is diagonal), then over the rows
+            rows = plan.N // (2 * prob.K[-1])
+            flops = 8.0 * (plan.N * npts[1] + rows * npts[0] * npts[1])
             tf = flops / (ms / 1e3) / 1e12
             res.append({"case": name, "N": plan.N, "grid": npts, "ms": ms, "tflops": tf,
                         "frac_fp64_mfma_peak": tf / FP64_MFMA_PEAK_TFLOPS, "E0": float(r.evals[0])})

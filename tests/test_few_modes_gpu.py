@@ -218,6 +218,30 @@ def test_batch_of_all_kinds(graph, prec):
         p.close()
 
 
+@pytest.mark.parametrize("d,plans", [(1, 9), (2, 9), (2, 3), (3, 5)])
+def test_batch_deals_items_over_xcds(d, plans):
+    """Items of one kind whose groups end at every XCD, with and without
+    vectors: each result equals the plan's own apply."""
+    P, K, L = {1: (P1, [9], [40]), 2: (P4, [3, 4], [6, 5]), 3: (P6, [2, 2, 3], [3, 2, 2])}[d]
+    probs = [star(P, [K[0] + i % 3] + K[1:], L, seed=i) for i in range(plans)]
+    ps = [lib.Plan.from_problem(p) for p in probs]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        batch = lib.Batch(ps, precision="fp64", graph=False)
+        for rep in range(3):
+            print(f"case: batch over XCDs d={d} plans={plans} rep {rep}", flush=True)
+            xs = [None if (i + rep) % 4 == 3 else block(p.N, 1 + (2 * i + rep) % 9, seed=i) for i, p in enumerate(probs)]
+            ys = [None if x is None else torch.full_like(x, float("nan")) for x in xs]
+            batch.apply(xs, ys)
+            refs = [None if x is None else p.apply(x) for p, x in zip(ps, xs)]
+            torch.cuda.synchronize()
+            for i, (y, r) in enumerate(zip(ys, refs)):
+                assert y is None or torch.equal(y, r), i
+        batch.close()
+    for p in ps:
+        p.close()
+
+
 def test_under_capture_and_tuned():
     """A captured apply replays on new data; tuning a plan that has nothing to
     choose leaves its results alone."""
