@@ -385,8 +385,8 @@ int iwfpm_dense_heev_lowest(int n, int nv, const double* A, double* w, double* V
  *     f4 = h^2/(h^2 + S2), f5 = nu/h, f6 = log(1 + e_max)/8,
  *     f7 = sqrt(e)/(sqrt(e) + sqrt(nu))       (0/0 read as 0).
  * Weight matrices are stored in bfloat16 (round to nearest even from the
- * float32 masters) and multiplied with float32 accumulation; biases, beta and
- * the optimiser state (Adam) are float32.  A new network reproduces M exactly
+ * float32 masters) and multiplied with float32 accumulation (float64 in the
+ * gradient); biases, beta and the optimiser state (Adam) are float32.  A new network reproduces M exactly
  * (last layer zero, beta = 0).
  *
  * Parameter vector (float32, iwfpm_learned_nparams entries), in order: for

@@ -53,7 +53,7 @@ struct LearnedPrecond {
     std::vector<float> h_feat;
     DeviceBuf shell, feat, M, D0, E;
     DeviceBuf act;    // Z1 Y1 Z2 Y2 Z3 Y3 (S x H each), O (S x 2)
-    DeviceBuf bwd;    // two S x H scratch arrays, dO as float (S x 2)
+    DeviceBuf bwd;    // two S x H scratch arrays (double)
     DeviceBuf red;    // dO (S x 2 double), dbeta (3), flag
     DeviceBuf work;   // wblocks blocks of wcols columns
     DeviceBuf small, partial;  // coefficients of combinations, Gram partial sums (training)
@@ -176,7 +176,7 @@ static int lp_build(LearnedPrecond* lp, iwfpm_plan_s* p, int S) {
         dev_alloc(lp->M, N * sizeof(double)) || dev_alloc(lp->D0, N * sizeof(double)) ||
         dev_alloc(lp->E, N * sizeof(double)) ||
         dev_alloc(lp->act, ((size_t)6 * S * kHid + 2 * S) * sizeof(float)) ||
-        dev_alloc(lp->bwd, ((size_t)2 * S * kHid + 2 * S) * sizeof(float)) ||
+        dev_alloc(lp->bwd, (size_t)2 * S * kHid * sizeof(double)) ||
         dev_alloc(lp->red, red_doubles(S) * sizeof(double)))
         return IWFPM_ERR_ALLOC;
     if (hipMemcpy(lp->shell.ptr, lp->h_shell.data(), N * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
@@ -394,14 +394,13 @@ static int lp_backprop(LearnedPrecond* lp, const double2* G, const double2* R, c
     // back through the MLP
     float* g = (float*)n->g.ptr;
     const uint16_t* wbf = (const uint16_t*)n->wbf.ptr;
-    float* dcur = (float*)lp->bwd.ptr + (size_t)2 * S * kHid;  // dO as float, S x 2
-    float* s0 = (float*)lp->bwd.ptr;
-    float* s1 = s0 + (size_t)S * kHid;
-    if (lp_to_float(red_dO(lp), dcur, 2 * S, 1.0, st) != hipSuccess) return IWFPM_ERR_DEVICE;
+    const double* dcur = red_dO(lp);
+    double* s0 = (double*)lp->bwd.ptr;
+    double* s1 = s0 + (size_t)S * kHid;
     if (lp_beta_grad(red_dbeta(lp), beta, g + n->offbeta, st) != hipSuccess) return IWFPM_ERR_DEVICE;
     for (int l = kLayers - 1; l >= 0; --l) {
         const float* X = l == 0 ? (const float*)lp->feat.ptr : act_at(lp, 2 * (l - 1) + 1);
-        float* dX = l == 0 ? nullptr : (dcur == s0 ? s1 : s0);
+        double* dX = l == 0 ? nullptr : (dcur == s0 ? s1 : s0);
         // dZ_{l-1} = dY_{l-1} .* GELU'(Z_{l-1})
         const float* Zin = l == 0 ? nullptr : act_at(lp, 2 * (l - 1));
         if (lp_dense_bwd(X, dcur, wbf + n->offw[l], Zin, dX, g + n->offw[l], g + n->offb[l], S, n->in[l], n->out[l],

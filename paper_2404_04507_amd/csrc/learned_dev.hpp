@@ -11,13 +11,14 @@
 
 namespace iwfpm {
 
-// ---- dense layers of the shell MLP: bfloat16 weights on the bf16 matrix cores, float32 accumulation ----
+// ---- dense layers of the shell MLP: bfloat16 weights; forward on the bf16 matrix cores with float32
+// accumulation, backward in float64 ----
 // Y[s][o] = act(sum_i X[s][i] W[i][o] + b[o]) for s < S; Z (optional) keeps the pre-activation
 hipError_t lp_dense_fwd(const float* X, const uint16_t* W, const float* b, float* Z, float* Y, int S, int in, int out,
                         int act, hipStream_t st);
 // dX = (dZ W^T) .* GELU'(Zin), Zin the pre-activations of the layer below (skipped when dX is null),
 // dW = X^T dZ, db = column sums of dZ
-hipError_t lp_dense_bwd(const float* X, const float* dZ, const uint16_t* W, const float* Zin, float* dX, float* dW,
+hipError_t lp_dense_bwd(const float* X, const double* dZ, const uint16_t* W, const float* Zin, double* dX, float* dW,
                         float* db, int S, int in, int out, hipStream_t st);
 // Adam on float32 master weights w (moments m, v) with bias corrections c1, c2;
 // refreshes the bfloat16 copy wbf
@@ -50,8 +51,6 @@ hipError_t lp_shell_grad(const double2* G, const double2* R, const double2* A, c
                          hipStream_t st);
 // g[0..1] = gradient of (beta0, beta1) from the three sums of lp_shell_grad
 hipError_t lp_beta_grad(const double* dbeta, const float* beta, float* g, hipStream_t st);
-// b[i] = float(a[i] * scale)
-hipError_t lp_to_float(const double* a, float* b, int n, double scale, hipStream_t st);
 // flag[0] = 1 if any of the n floats is not finite (flag zeroed by the caller)
 hipError_t lp_nonfinite(const float* a, int n, int* flag, hipStream_t st);
 hipError_t lp_nonfinite_d(const double* a, long long n, int* flag, hipStream_t st);

@@ -12,10 +12,10 @@
 // with M the diagonal of eq:precond and (o0, o1) the two outputs of a small
 // MLP (3 hidden layers, GELU) evaluated once per kinetic-energy shell.  D0
 // never drops below M/2, so every component of the residual keeps at least
-// half of its plain-preconditioned weight.  MLP
-// weights are stored in bfloat16; every product accumulates in float32 and the
-// optimiser keeps float32 master weights (Adam).  Grid-sized arithmetic is in
-// float64 like the rest of the eigensolver's block algebra.
+// half of its plain-preconditioned weight.  MLP weights are stored in bfloat16;
+// the forward products accumulate in float32, the backward ones in float64, and
+// the optimiser keeps float32 master weights (Adam).  Grid-sized arithmetic is
+// in float64 like the rest of the eigensolver's block algebra.
 
 #include <hip/hip_runtime.h>
 
@@ -35,9 +35,9 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 // GELU(x) = x Phi(x) (exact form) and its derivative Phi(x) + x phi(x)
 __device__ __forceinline__ float gelu(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad(float x) {
-    float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-    float pdf = 0.39894228040143268f * expf(-0.5f * x * x);
+__device__ __forceinline__ double gelu_grad(double x) {
+    const double cdf = 0.5 * (1.0 + erf(x * 0.70710678118654752));
+    const double pdf = 0.39894228040143268 * exp(-0.5 * x * x);
     return cdf + x * pdf;
 }
 
@@ -61,24 +61,27 @@ __device__ __forceinline__ float gelu_grad(float x) {
 // would follow every change of its rounding.  Only the loads changed: 64
 // values of K at a time, the next 64 in flight.
 //
-// Backward (k_mlp_gemm): a workgroup takes a 32 x 32 tile and its waves split K
-// in steps of 32 (v_mfma_f32_16x16x32_bf16: lane l holds k = 8(l/16) ..
-// 8(l/16)+7 of row or column l%16, the result as above), each with the next
-// step's loads in flight; the waves' tiles are added in LDS in a fixed order,
-// where GELU's derivative is applied.  The bias gradient is one more row of
-// X^T, of ones.
+// Backward (k_mlp_dx, k_mlp_dw): float64 on the matrix cores
+// (v_mfma_f64_16x16x4f64: lane l holds A[l%16][l/16] and B[l/16][l%16] and ends
+// with D[l/16 + 4v][l%16], v < 4).  The shells' gradients cancel when they are
+// summed (at weak coupling sum |dO| is hundreds of times |sum dO|, and more), so
+// sums in float32 lose digits that the result needs.  Error of the gradient
+// against 64 bits (norms; 37 cases, couplings 0.1 to 10, 2 to 12 columns): 0.29e-6
+// to 2.3e-6 with float32 sums over 16 values of K a step, 0.08e-6 to 2.5e-6 over
+// 32 a step, 0.03e-6 to 2.2e-6 now and in no case larger than either; what is
+// left is the float32 forward pass.  A workgroup takes a 16 x 16 tile and its
+// waves split K, each with the next step's loads in flight; their tiles are
+// added in LDS in a fixed order, where GELU's derivative is applied.  The bias
+// gradient is one more row of X^T, of ones.
 //
-// Loss and gradient of a 65,536-point plan: 2,079 us in all before (the
-// products 660, the bias sums 587), 463 now (forward 14 us a product where it
-// runs, backward 7 and 15).
+// Loss and gradient of a 65,536-point plan: 2,079 us with a wave per tile that
+// loads K element by element (the products 660, the bias sums 587), 414 now
+// (forward 14 us a product where it runs, backward 14 and 11; 436 with the split
+// float32 products).
 // ---------------------------------------------------------------------------
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kMlpTile = 32;
-constexpr int kMlpWaves = 8;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // x = h + m + l in bfloat16 (exact for normal float32 x; round to nearest even
 // in hardware, v_cvt_pk_bf16_f32)
@@ -90,41 +93,6 @@ __device__ __forceinline__ void split3(float x, short& h, short& m, short& l) {
     h = __builtin_bit_cast(short, a);
     m = __builtin_bit_cast(short, b);
     l = __builtin_bit_cast(short, (__bf16)r2);
-}
-
-// eight values k .. k + 7 (zero past K) of row r of an operand stored with k
-// contiguous (T: float or bfloat16), or of column r of one stored with k as rows
-template <typename T>
-__device__ __forceinline__ void mlp_load(const T* __restrict__ p, int ld, bool kcontig, bool vec, int r, int R, int k,
-                                         int K, float (&x)[8]) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) x[q] = 0.f;
-    if (k >= K) return;
-    if (kcontig && vec) {  // K a multiple of 8, rows aligned to 16 bytes
-        if (r >= R) return;
-        const T* s = p + (size_t)r * ld + k;
-        if constexpr (sizeof(T) == 4) {
-            const float4 a = reinterpret_cast<const float4*>(s)[0], b = reinterpret_cast<const float4*>(s)[1];
-            x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-            x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-        } else {
-            const s16x8 v = *reinterpret_cast<const s16x8*>(s);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = bf2f((uint16_t)v[q]);
-        }
-        return;
-    }
-    // loads from the last row or value there is, so that none waits for a branch
-    const int rr = min(r, R - 1);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int kk = min(k + q, K - 1);
-        const size_t e = kcontig ? (size_t)rr * ld + kk : (size_t)kk * ld + rr;
-        float v;
-        if constexpr (sizeof(T) == 4) v = p[e];
-        else v = bf2f(p[e]);
-        x[q] = r < R && k + q < K ? v : 0.f;
-    }
 }
 
 // C (M x N) = A (M x K, float32, row-major) B (K x N, bfloat16, row-major) +
@@ -204,120 +172,130 @@ __global__ void __launch_bounds__(64) k_mlp_fwd(const float* __restrict__ A, con
     }
 }
 
-struct MlpGemm {
-    const float* A;      // M x K; a_k: k contiguous (row stride lda), else stored K x M
-    const void* B;       // K x N, TB; b_k: k contiguous (stored N x K), else row stride ldb
-    float* Y;            // the sums, times GELU'(dact) where that is given
-    const float* dact;   // pre-activations (M x N), or null
-    float* ones;         // null, or where row M - 1 goes: A's last row is then all ones
-    int M, N, K, lda, ldb, a_k, b_k, a_vec, b_vec;
-};
+constexpr int kMlpWaves = 8;
 
-template <typename TB>
-__global__ void __launch_bounds__(64 * kMlpWaves) k_mlp_gemm(MlpGemm g) {
-    __shared__ float red[kMlpWaves][kMlpTile][kMlpTile + 1];
+// the workgroup's tile: every wave's part, added up in wave order; element e of
+// the tile (row e / 16, column e % 16) goes to thread e
+__device__ __forceinline__ double mlp_tile_sum(const f64x4& acc, double (&red)[kMlpWaves][16][17]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int li = lane & 15, lk = 8 * (lane >> 4);
-    const int tiles_n = (g.N + kMlpTile - 1) / kMlpTile;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][(lane >> 4) + 4 * v][lane & 15] = acc[v];
+    __syncthreads();
+    double z = 0.0;
+    if (threadIdx.x < 256)
+        for (int w = 0; w < kMlpWaves; ++w) z += red[w][threadIdx.x >> 4][threadIdx.x & 15];
+    return z;
+}
+
+// dX (S x in) = dZ (S x out) W^T .* GELU'(Zin), W (in x out) bfloat16.  A lane's
+// four steps of a round take four neighbouring k, the same for both operands;
+// vec: out is a multiple of 4 and rows start on 16 (dZ) and 8 bytes (W)
+__global__ void __launch_bounds__(64 * kMlpWaves) k_mlp_dx(const double* __restrict__ dZ,
+                                                           const uint16_t* __restrict__ W,
+                                                           const float* __restrict__ Zin, double* __restrict__ dX,
+                                                           int S, int in, int out, int vec) {
+    __shared__ double red[kMlpWaves][16][17];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane & 15, lk = 4 * (lane >> 4);
+    const int tiles_n = (in + 15) >> 4;
     const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
-    const int r0 = tm * kMlpTile, c0 = tn * kMlpTile;
-    const int Ma = g.ones ? g.M - 1 : g.M;  // rows that A holds
-    const TB* B = reinterpret_cast<const TB*>(g.B);
-    f32x4 acc[2][2];
+    const int s = tm * 16 + li, i = tn * 16 + li;
+    const double* a = dZ + (size_t)min(s, S - 1) * out;
+    const uint16_t* b = W + (size_t)min(i, in - 1) * out;
+    // loads from the last row or values there are, so that none waits for a branch
+    auto fetch = [&](int k0, double (&x)[4], uint16_t (&w)[4]) {
+        if (vec) {
+            const int k = min(k0 + lk, out - 4);
+            const double2 x0 = reinterpret_cast<const double2*>(a + k)[0], x1 = reinterpret_cast<const double2*>(a + k)[1];
+            const ushort4 wv = *reinterpret_cast<const ushort4*>(b + k);
+            x[0] = x0.x; x[1] = x0.y; x[2] = x1.x; x[3] = x1.y;
+            w[0] = wv.x; w[1] = wv.y; w[2] = wv.z; w[3] = wv.w;
+            return;
+        }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto fetch = [&](int k0, float (&a)[2][8], float (&b)[2][8]) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int r = r0 + 16 * t + li;
-            mlp_load<float>(g.A, g.lda, g.a_k, g.a_vec, r, Ma, k0 + lk, g.K, a[t]);
-            if (g.ones && r == g.M - 1)
-#pragma unroll
-                for (int q = 0; q < 8; ++q) a[t][q] = k0 + lk + q < g.K ? 1.f : 0.f;
-            mlp_load<TB>(B, g.ldb, g.b_k, g.b_vec, c0 + 16 * t + li, g.N, k0 + lk, g.K, b[t]);
+        for (int q = 0; q < 4; ++q) {
+            const int k = min(k0 + lk + q, out - 1);
+            x[q] = a[k];
+            w[q] = b[k];
         }
     };
-    float a[2][8], b[2][8];
-    const int step = 32 * kMlpWaves;
-    int k0 = 32 * wave;
-    if (k0 < g.K) fetch(k0, a, b);
-    for (; k0 < g.K; k0 += step) {
-        float an[2][8], bn[2][8];
-        if (k0 + step < g.K) fetch(k0 + step, an, bn);
-        bf16x8 ah[2], am[2], al[2], bh[2], bm[2], bl[2];
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    double x[4];
+    uint16_t w[4];
+    int k0 = 16 * wave;
+    if (k0 < out) fetch(k0, x, w);
+    for (; k0 < out; k0 += 16 * kMlpWaves) {
+        double xn[4];
+        uint16_t wn[4];
+        fetch(k0 + 16 * kMlpWaves, xn, wn);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            s16x8 h, m, l;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                short x, y, z;
-                split3(a[t][q], x, y, z);
-                h[q] = x;
-                m[q] = y;
-                l[q] = z;
-            }
-            ah[t] = __builtin_bit_cast(bf16x8, h);
-            am[t] = __builtin_bit_cast(bf16x8, m);
-            al[t] = __builtin_bit_cast(bf16x8, l);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                short x, y = 0, z = 0;
-                if constexpr (sizeof(TB) == 4) split3(b[t][q], x, y, z);
-                else x = (short)(__float_as_uint(b[t][q]) >> 16);
-                h[q] = x;
-                m[q] = y;
-                l[q] = z;
-            }
-            bh[t] = __builtin_bit_cast(bf16x8, h);
-            bm[t] = __builtin_bit_cast(bf16x8, m);
-            bl[t] = __builtin_bit_cast(bf16x8, l);
+        for (int q = 0; q < 4; ++q) {
+            const bool ok = k0 + lk + q < out;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ok && s < S ? x[q] : 0.0,
+                                                       ok && i < in ? (double)bf2f(w[q]) : 0.0, acc, 0, 0, 0);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[i], bh[j], acc[i][j], 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh[j], acc[i][j], 0, 0, 0);
-                if constexpr (sizeof(TB) == 4) {
-                    // float32 x float32: the six largest of the nine terms
-                    // (what is left is below 2^-23 of each product)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bm[j], acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[i], bm[j], acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl[j], acc[i][j], 0, 0, 0);
-                }
-            }
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                a[t][q] = an[t][q];
-                b[t][q] = bn[t][q];
-            }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) red[wave][16 * i + 4 * (lane >> 4) + v][16 * j + li] = acc[i][j][v];
-    __syncthreads();
-    const int waves = min(kMlpWaves, (g.K + 31) / 32);  // the others' tiles are zero
-    for (int e = threadIdx.x; e < kMlpTile * kMlpTile; e += blockDim.x) {
-        const int i = e / kMlpTile, j = e - i * kMlpTile;
-        const int r = r0 + i, c = c0 + j;
-        if (r >= g.M || c >= g.N) continue;
-        float z = red[0][i][j];
-        for (int w = 1; w < waves; ++w) z += red[w][i][j];
-        if (g.ones && r == g.M - 1) {
-            g.ones[c] = z;
-            continue;
+        for (int q = 0; q < 4; ++q) {
+            x[q] = xn[q];
+            w[q] = wn[q];
         }
-        const size_t o = (size_t)r * g.N + c;
-        g.Y[o] = g.dact ? z * gelu_grad(g.dact[o]) : z;
     }
+    const double z = mlp_tile_sum(acc, red);
+    const int r = tm * 16 + (threadIdx.x >> 4), c = tn * 16 + (threadIdx.x & 15);
+    if (threadIdx.x >= 256 || r >= S || c >= in) return;
+    const size_t e = (size_t)r * in + c;
+    dX[e] = z * gelu_grad((double)Zin[e]);
+}
+
+// dW (in x out) = X^T dZ, X (S x in), and db (out) = the column sums of dZ as row
+// `in` of the product
+__global__ void __launch_bounds__(64 * kMlpWaves) k_mlp_dw(const float* __restrict__ X,
+                                                           const double* __restrict__ dZ, float* __restrict__ dW,
+                                                           float* __restrict__ db, int S, int in, int out) {
+    __shared__ double red[kMlpWaves][16][17];
+    constexpr int U = 8;  // steps of 4 loaded together
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int tiles_n = (out + 15) >> 4;
+    const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
+    const int i = tm * 16 + li, o = tn * 16 + li;
+    const float* a = X + min(i, in - 1);
+    const double* b = dZ + min(o, out - 1);
+    auto fetch = [&](int s0, float (&x)[U], double (&d)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t s = min(s0 + 4 * u + lk, S - 1);
+            x[u] = a[s * in];
+            d[u] = b[s * out];
+        }
+    };
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    float x[U];
+    double d[U];
+    constexpr int step = 4 * U * kMlpWaves;
+    int s0 = 4 * U * wave;
+    if (s0 < S) fetch(s0, x, d);
+    for (; s0 < S; s0 += step) {
+        float xn[U];
+        double dn[U];
+        fetch(s0 + step, xn, dn);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool ok = s0 + 4 * u + lk < S;
+            const double av = i < in ? (double)x[u] : (i == in ? 1.0 : 0.0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ok ? av : 0.0, ok && o < out ? d[u] : 0.0, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = xn[u];
+            d[u] = dn[u];
+        }
+    }
+    const double z = mlp_tile_sum(acc, red);
+    const int r = tm * 16 + (threadIdx.x >> 4), c = tn * 16 + (threadIdx.x & 15);
+    if (threadIdx.x >= 256 || r > in || c >= out) return;
+    if (r == in) db[c] = (float)z;
+    else dW[(size_t)r * out + c] = (float)z;
 }
 
 __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v, const float* __restrict__ g,
@@ -466,11 +444,6 @@ __global__ void k_beta_grad(const double* __restrict__ dbeta, const float* __res
     g[1] = (float)(2.0 * lc.a * g0 + g1 + lc.a * lc.a * gd);
 }
 
-__global__ void k_to_float(const double* __restrict__ a, float* __restrict__ b, int n, double scale) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) b[e] = (float)(a[e] * scale);
-}
-
 __global__ void k_nonfinite(const float* __restrict__ a, int n, int* __restrict__ flag) {
     int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e < n && !isfinite(a[e])) atomicOr(flag, 1);
@@ -491,31 +464,21 @@ static int blocks_for(long long n, int cap) {
 constexpr int kGridCap = 4096;
 constexpr int kNoCap = 1 << 30;
 
-static int mlp_blocks(const MlpGemm& g) {
-    return ((g.M + kMlpTile - 1) / kMlpTile) * ((g.N + kMlpTile - 1) / kMlpTile);
-}
-// rows of ld elements of `esz` bytes at p start on 16 bytes and hold whole groups of eight
-static int mlp_vec(const void* p, int ld, int K, int esz) {
-    return K % 8 == 0 && ld * esz % 16 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
-}
+static int mlp_tiles(int M, int N) { return ((M + 15) / 16) * ((N + 15) / 16); }
 
 hipError_t lp_dense_fwd(const float* X, const uint16_t* W, const float* b, float* Z, float* Y, int S, int in, int out,
                         int act, hipStream_t st) {
     const int vec = in % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-    k_mlp_fwd<<<((S + 15) / 16) * ((out + 15) / 16), 64, 0, st>>>(X, W, b, Z, Y, S, out, in, act, vec);
+    k_mlp_fwd<<<mlp_tiles(S, out), 64, 0, st>>>(X, W, b, Z, Y, S, out, in, act, vec);
     return hipGetLastError();
 }
-hipError_t lp_dense_bwd(const float* X, const float* dZ, const uint16_t* W, const float* Zin, float* dX, float* dW,
+hipError_t lp_dense_bwd(const float* X, const double* dZ, const uint16_t* W, const float* Zin, double* dX, float* dW,
                         float* db, int S, int in, int out, hipStream_t st) {
     if (dX) {
-        // dX (S x in) = dZ (S x out) W^T, times GELU'(Zin)
-        const MlpGemm g{dZ, W, dX, Zin, nullptr, S, in, out, out, out, 1, 1, mlp_vec(dZ, out, out, 4),
-                        mlp_vec(W, out, out, 2)};
-        k_mlp_gemm<uint16_t><<<mlp_blocks(g), 64 * kMlpWaves, 0, st>>>(g);
+        const int vec = out % 4 == 0 && reinterpret_cast<uintptr_t>(dZ) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 8 == 0;
+        k_mlp_dx<<<mlp_tiles(S, in), 64 * kMlpWaves, 0, st>>>(dZ, W, Zin, dX, S, in, out, vec);
     }
-    // [dW; db] (in + 1 rows x out) = [X 1]^T (in + 1 x S) dZ (S x out)
-    const MlpGemm g{X, dZ, dW, nullptr, db, in + 1, out, S, in, out, 0, 0, 0, 0};
-    k_mlp_gemm<float><<<mlp_blocks(g), 64 * kMlpWaves, 0, st>>>(g);
+    k_mlp_dw<<<mlp_tiles(in + 1, out), 64 * kMlpWaves, 0, st>>>(X, dZ, dW, db, S, in, out);
     return hipGetLastError();
 }
 hipError_t lp_adam(float* w, float* m, float* v, const float* g, uint16_t* wbf, int n, float lr, float b1, float b2,
@@ -555,10 +518,6 @@ hipError_t lp_shell_grad(const double2* G, const double2* R, const double2* A, c
 }
 hipError_t lp_beta_grad(const double* dbeta, const float* beta, float* g, hipStream_t st) {
     k_beta_grad<<<1, 64, 0, st>>>(dbeta, beta, g);
-    return hipGetLastError();
-}
-hipError_t lp_to_float(const double* a, float* b, int n, double scale, hipStream_t st) {
-    k_to_float<<<blocks_for(n, kNoCap), 256, 0, st>>>(a, b, n, scale);
     return hipGetLastError();
 }
 hipError_t lp_nonfinite_d(const double* a, long long n, int* flag, hipStream_t st) {
