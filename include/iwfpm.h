@@ -112,8 +112,10 @@ const char* iwfpm_status_string(int status);
  * k_I axes and the precision) is applied without transforms, as the
  * wrapped convolution sum_m Vhat_m psi[(k* - m) mod ext] that F V F^{-1}
  * equals, in float64 and without a workspace; a named schedule always runs
- * the transforms, and so do the eigensolvers.  Host inputs (P, K, L, modes, vhat) are copied; the caller may free
- * them on return.  opts may be NULL (defaults).  Blocking.
+ * the transforms, and so do the eigensolvers, their learned preconditioner
+ * included (iwfpm_learned_forward, _grad, _step and the steps of _train take
+ * the plan's own route).  Host inputs (P, K, L, modes, vhat) are copied; the
+ * caller may free them on return.  opts may be NULL (defaults).  Blocking.
  * Errors: ERR_ARG (d < 1, n <= d, n > 8, K/L < 1, non-finite P or vhat),
  * ERR_UNSUPPORTED (a grid extent 2K_j or 2L_j the library has no transform
  * for, or more than 2^31 - 1 grid points), ERR_SINGULAR_PI, ERR_NONHERMITIAN,
@@ -386,8 +388,8 @@ int iwfpm_dense_heev_lowest(int n, int nv, const double* A, double* w, double* V
  *     f7 = sqrt(e)/(sqrt(e) + sqrt(nu))       (0/0 read as 0).
  * Weight matrices are stored in bfloat16 (round to nearest even from the
  * float32 masters) and multiplied with float32 accumulation (float64 in the
- * gradient); biases, beta and the optimiser state (Adam) are float32.  A new network reproduces M exactly
- * (last layer zero, beta = 0).
+ * gradient); biases, beta and the optimiser state (Adam) are float32.  A new
+ * network reproduces M exactly (last layer zero, beta = 0).
  *
  * Parameter vector (float32, iwfpm_learned_nparams entries), in order: for
  * layers l = 1..4 with (in, out) = (F, H), (H, H), (H, H), (H, 2): W_l

@@ -249,22 +249,22 @@ static int lp_ensure_work(LearnedPrecond* lp, int m, int blocks) {
 
 static double2* wblock(LearnedPrecond* lp, int b) { return (double2*)lp->work.ptr + (size_t)b * lp->wcols * lp->N; }
 
-static int conv(LearnedPrecond* lp, const double2* in, double2* out, int m, hipStream_t st) {
-    return plan_apply(lp->plan, in, out, m, lp->conv_prec, st, 0);
+static int conv(LearnedPrecond* lp, const double2* in, double2* out, int m, hipStream_t st, bool transforms = false) {
+    return plan_apply(lp->plan, in, out, m, lp->conv_prec, st, 0, transforms);
 }
 
 // A = C(E R), Cc = C(E A) and W = (D0 + b1 a^2 E) R + E (2 a b1 A + b1 Cc); R, W as column pointers
 static int lp_forward(LearnedPrecond* lp, const ColPtrs& R, const ColPtrs& W, int m, double2* A, double2* Cc,
-                      hipStream_t st) {
+                      hipStream_t st, bool transforms = false) {
     int rc = lp_forward_mlp(lp, st);
     if (rc) return rc;
     const double* D0 = (const double*)lp->D0.ptr;
     const double* E = (const double*)lp->E.ptr;
     double2* tmp = wblock(lp, WB_TMP);
     if (lp_scale_cols(R, tmp, m, E, lp->N, st) != hipSuccess) return IWFPM_ERR_DEVICE;
-    if ((rc = conv(lp, tmp, A, m, st))) return rc;
+    if ((rc = conv(lp, tmp, A, m, st, transforms))) return rc;
     if (lp_scale(A, tmp, m, E, lp->N, st) != hipSuccess) return IWFPM_ERR_DEVICE;
-    if ((rc = conv(lp, tmp, Cc, m, st))) return rc;
+    if ((rc = conv(lp, tmp, Cc, m, st, transforms))) return rc;
     const float* beta = (const float*)lp->net->w32.ptr + lp->net->offbeta;
     if (lp_combine(R, A, Cc, W, m, D0, E, beta, lp->N, st) != hipSuccess) return IWFPM_ERR_DEVICE;
     return IWFPM_OK;
@@ -543,12 +543,13 @@ bool learned_ready(const LearnedPrecond* lp, const iwfpm_plan_s* p) {
     return lp && lp->net && lp->plan == p && lp->N == p->geom.N;
 }
 
-int learned_apply(LearnedPrecond* lp, iwfpm_plan_s* p, const ColPtrs& R, const ColPtrs& W, int m, hipStream_t st) {
+int learned_apply(LearnedPrecond* lp, iwfpm_plan_s* p, const ColPtrs& R, const ColPtrs& W, int m, bool transforms,
+                  hipStream_t st) {
     if (!learned_ready(lp, p)) return IWFPM_ERR_WEIGHTS;
     if (m == 0) return IWFPM_OK;
     int rc = lp_ensure_work(lp, m, 3);
     if (rc) return rc;
-    return lp_forward(lp, R, W, m, wblock(lp, WB_A), wblock(lp, WB_C), st);
+    return lp_forward(lp, R, W, m, wblock(lp, WB_A), wblock(lp, WB_C), st, transforms);
 }
 
 void learned_free(LearnedPrecond* lp) {
@@ -720,7 +721,7 @@ int iwfpm_learned_forward(iwfpm_plan_t p, const void* r, void* t, int nvec, void
     if (!guard.ok) return IWFPM_ERR_DEVICE;
     const long long N = p->geom.N;
     return learned_apply(p->learned, p, contiguous_cols((const double2*)r, nvec, N),
-                         contiguous_cols((const double2*)t, nvec, N), nvec, (hipStream_t)stream);
+                         contiguous_cols((const double2*)t, nvec, N), nvec, false, (hipStream_t)stream);
 }
 
 int iwfpm_learned_grad(iwfpm_plan_t p, const void* x, int nvec, const double* lam, double* loss, float* grad,

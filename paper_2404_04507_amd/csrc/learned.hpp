@@ -17,8 +17,10 @@ struct LearnedPrecond;
 
 // true when a network is attached and its weights are usable
 bool learned_ready(const LearnedPrecond* lp, const iwfpm_plan_s* p);
-// W_j = T(R_j) for j < m; returns IWFPM_OK or an error (the caller falls back to M)
-int learned_apply(LearnedPrecond* lp, iwfpm_plan_s* p, const ColPtrs& R, const ColPtrs& W, int m, hipStream_t st);
+// W_j = T(R_j) for j < m; returns IWFPM_OK or an error (the caller falls back to M).
+// transforms: its convolutions run the transforms on every plan, as a solve's applies do
+int learned_apply(LearnedPrecond* lp, iwfpm_plan_s* p, const ColPtrs& R, const ColPtrs& W, int m, bool transforms,
+                  hipStream_t st);
 void learned_free(LearnedPrecond* lp);
 
 // Iterates recorded by a plain solve (training data): every `stride`

@@ -1924,7 +1924,7 @@ static int tall_precondition(Tall& t, std::vector<BInst>& in, const std::vector<
                     w.p[a] = b.c.col(B_W, a);
                 }
             }
-            if (learned_apply(b.lp, b.p, r, w, ncol, b.c.st) == IWFPM_OK) {
+            if (learned_apply(b.lp, b.p, r, w, ncol, true, b.c.st) == IWFPM_OK) {
                 b.lp_used = true;
                 continue;
             }
