@@ -202,7 +202,7 @@ int iwfpm_conv(iwfpm_plan_t plan, const void* psi, void* out, int nvec, int prec
  * phases are reduced to one turn before the sine and cosine.  Asynchronous on
  * `stream` after a one-time set-up per plan (the frequencies P k of the
  * window points, computed on the host and copied synchronously) and growth of
- * the plan's scratch (per-axis tables of about 256 MB plus slice partials of
+ * the plan's scratch (per-axis tables of up to 256 MB plus slice partials of
  * up to 512 MB), which synchronises `stream` when it reallocates.  Not
  * re-entrant per plan (shared scratch).
  * Errors: ERR_ARG (NULL pointers, npts < 1, non-finite origin or step, too

@@ -204,13 +204,13 @@ __global__ void k_ef_zero(long long total, double2* __restrict__ out) {
         out[e] = make_double2(0.0, 0.0);
 }
 
-// T[(s, r)][c] of slices [s0, s0 + gridDim.y): a workgroup takes one slice and
-// 64 columns; the slice's exponentials of kEfRow positions at a time go to LDS
+// T[(s, r)][c] of rows [ra, ra + rc) of slices [s0, s0 + gridDim.y): a workgroup
+// takes one slice and 64 columns; the slice's exponentials of kEfRow positions at a time go to LDS
 // and each wave sums four rows per LDS read (the four products of a read
 // cover its LDS time), U at wave-uniform addresses.
 constexpr int kEfRow = 32;
 __global__ void __launch_bounds__(256) k_ef_rows(const double* __restrict__ f, const double2* __restrict__ U, int s0,
-                                                 int Rs, int El, int nc, double o, double h,
+                                                 int Rs, int ra, int rc, int El, int nc, double o, double h,
                                                  double2* __restrict__ T) {
     __shared__ double2 E[kEfRow][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(256) k_ef_rows(const double* __restrict__ f, c
     const int sl = blockIdx.y;
     const long long s = s0 + sl;
     const double xi = o + h * (double)c;
-    for (int r0 = 0; r0 < Rs; r0 += 16) {
+    for (int r0 = 0; r0 < rc; r0 += 16) {
         const int r = r0 + 4 * wave;
         double2 acc[4];
 #pragma unroll
@@ -236,8 +236,8 @@ __global__ void __launch_bounds__(256) k_ef_rows(const double* __restrict__ f, c
                 }
                 __syncthreads();
             }
-            const double2* u = U + (s * Rs + r) * El + p0;
-            if (r + 4 <= Rs) {
+            const double2* u = U + (s * Rs + ra + r) * El + p0;
+            if (r + 4 <= rc) {
                 for (int q = 0; q < np; ++q) {
                     const double2 e = E[q][lane];
 #pragma unroll
@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(256) k_ef_rows(const double* __restrict__ f, c
                 }
             } else {
                 for (int v = 0; v < 4; ++v)
-                    if (r + v < Rs)
+                    if (r + v < rc)
                         for (int q = 0; q < np; ++q) {
                             const double2 e = E[q][lane], a = u[(long long)v * El + q];
                             acc[v].x += a.x * e.x - a.y * e.y;
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(256) k_ef_rows(const double* __restrict__ f, c
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            if (r + v < Rs && c < nc) T[((long long)sl * Rs + r + v) * nc + c] = acc[v];
+            if (r + v < rc && c < nc) T[((long long)sl * rc + r + v) * nc + c] = acc[v];
     }
 }
 
@@ -380,7 +380,8 @@ extern "C" int iwfpm_eigenfunction(iwfpm_plan_t p, const void* u, const double* 
     long long np = (long long)(kEfTableBudget / (sizeof(double2) * (size_t)row));
     np = std::max(4LL, np - np % 4);
     np = std::min(np, ((N + 3) / 4) * 4);
-    if (sep) np = std::max<long long>(1, std::min<long long>(np, 32768LL * Rs) / Rs) * Rs;  // whole slices
+    // rows: whole slices, or a part of one where a slice's tables are over the budget
+    if (sep && np > Rs) np = std::min<long long>(np, 32768LL * Rs) / Rs * Rs;
     // slices: enough workgroups for the chip, at least 64 window points each,
     // partials within their budget (one slice writes the output directly)
     // (two per CU: more slices only add partial grids, 16 MB each on 1001 x
@@ -405,8 +406,10 @@ extern "C" int iwfpm_eigenfunction(iwfpm_plan_t p, const void* u, const double* 
         k_ef_zero<<<grid_blocks(total), 256, 0, st>>>(total, o);
         return hipGetLastError() == hipSuccess ? IWFPM_OK : IWFPM_ERR_DEVICE;
     }
-    for (long long p0 = 0; p0 < N; p0 += np) {
-        const long long cnt = std::min(np, N - p0);
+    long long cnt = 0;
+    for (long long p0 = 0; p0 < N; p0 += cnt) {
+        cnt = std::min(np, N - p0);
+        if (sep && np < Rs) cnt = std::min(cnt, Rs - p0 % Rs);
         g.p0 = p0;
         g.np = cnt;
         // table offsets within the chunk buffer
@@ -419,8 +422,10 @@ extern "C" int iwfpm_eigenfunction(iwfpm_plan_t p, const void* u, const double* 
         }
         g.boff = off;
         if (sep) {
-            k_ef_rows<<<dim3((unsigned)g.tiles_c, (unsigned)(cnt / Rs)), 256, 0, st>>>(
-                f + (size_t)(d - 1) * N, g.U, (int)(p0 / Rs), Rs, El, g.nc, origin[d - 1], step[d - 1], tab + off);
+            const int rc = (int)std::min<long long>(cnt, Rs);
+            k_ef_rows<<<dim3((unsigned)g.tiles_c, (unsigned)(cnt / rc)), 256, 0, st>>>(
+                f + (size_t)(d - 1) * N, g.U, (int)(p0 / Rs), Rs, (int)(p0 % Rs), rc, El, g.nc, origin[d - 1],
+                step[d - 1], tab + off);
             if (d == 1) {  // the rows are the slices: their sum is the answer
                 k_ef_reduce<<<grid_blocks(total), 256, 0, st>>>(tab + off, (int)cnt, total, p0 > 0, o);
                 if (hipGetLastError() != hipSuccess) return IWFPM_ERR_DEVICE;
