@@ -67,7 +67,8 @@ __device__ __forceinline__ double stencil_kinetic(const double* P1, const double
 // k_I axis, the rotation taking the point's coordinate in its vector order to
 // the neighbour's.  In grid order that is -+ m_j; in window order the
 // coordinate counts from the slice's own lower window end a_j, so
-// p' = p + a_j -+ m_j - a'_j (mod the extent).
+// p' = p + a_j -+ m_j - a'_j (mod the extent); of the ends modulo the extent, as
+// ends of nearly 2^31 have no 32-bit difference.
 template <int D>
 __device__ __forceinline__ void stencil_tables(const DevGeom& g, const DevTabs& t, const StencilDesc& sd, int s0,
                                                int ns, int4* tab) {
@@ -94,7 +95,7 @@ __device__ __forceinline__ void stencil_tables(const DevGeom& g, const DevTabs& 
         for (int j = 0; j < D; ++j) {
             const int E = g.ext[nII + j], o = sd.off[m][nII + j];
             int v = (k & 1) ? o : -o;
-            if (g.order) v += t.slice_a[s * D + j] - t.slice_a[sn * D + j];
+            if (g.order) v += t.slice_m[s * D + j] - t.slice_m[sn * D + j];
             v %= E;
             dl[j] = v < 0 ? v + E : v;
         }
@@ -145,7 +146,7 @@ __device__ __forceinline__ void stencil_body(const DevGeom& g, const DevTabs& t,
             const int a = t.slice_a[s * D + j];
             int pj = (int)p[j];
             if (!g.order) {  // window coordinate of the grid coordinate
-                pj = (pj - a) % (int)E[j];
+                pj -= t.slice_m[s * D + j];
                 pj += pj < 0 ? (int)E[j] : 0;
             }
             kl[j] = (double)(a + pj);
