@@ -108,9 +108,10 @@ const char* iwfpm_status_string(int status);
  * block fits no workgroup either (e.g. 40^3 x 10^3), five: a further pass
  * transforms the axes between the two groups before and after the middle
  * one.  With IWFPM_SCHED_AUTO and no split or tile named, a potential of few
- * modes (one pair +-m per axis, or up to 4 to 16 pairs in all, by the number of
- * k_I axes and the precision) is applied without transforms, as the
- * wrapped convolution sum_m Vhat_m psi[(k* - m) mod ext] that F V F^{-1}
+ * modes (one pair +-m per axis, or up to 2 to 16 pairs in all, by the numbers of
+ * axes and points, the precision and how far the modes reach) is applied
+ * without transforms, as the wrapped convolution
+ * sum_m Vhat_m psi[(k* - m) mod ext] that F V F^{-1}
  * equals, in float64 and without a workspace; a named schedule always runs
  * the transforms, and so do the eigensolvers, their learned preconditioner
  * included (iwfpm_learned_forward, _grad, _step and the steps of _train take

@@ -443,21 +443,50 @@ static void build_star(iwfpm_plan_s* p) {
 }
 
 // Few-mode potentials take the wrapped convolution instead of transforms.
-// Its cost grows with the pairs of modes while the transforms' does not; the
-// lines lie where the convolution's lead is still sure on every grid of the
-// kind (us, convolution against transforms, graph replays on one card):
-//   float64, d <= 2: 12 pairs 211 : 335 (24^2 x 32^2, 16 vectors), 23 : 43
-//     (16^2 x 20^2, 6 vectors); 16 pairs 367 : 336 and 37 : 43
-//   float32, d <= 2: 8 pairs 131 : 164 and 18 : 28; 12 pairs 211 : 165 and 23 : 28
-//   d = 1: 16 pairs 17.5 : 69 (float64), : 61 (float32) on 1024 x 42, 8 vectors
-//   float64, d = 3: 4 pairs 90 : 153 (10^6, 5 vectors), 8 pairs 176 : 153
-//   float32, d = 3: 4 pairs 90 : 109, 8 pairs 176 : 109
-// A star is cheaper still and always takes it (16^6, 6 pairs, 3 vectors: 497
-// against 1,733 and 1,082).
-static int stencil_max_pairs(int d, int prec) {
-    if (d == 1) return 16;
-    if (d == 2) return prec ? 8 : 12;
-    return prec ? 4 : 6;
+// Its cost grows with the pairs of modes and with the number of slow axes that
+// these reach along (their neighbours come from the L2 and beyond), while the
+// transforms' does not: they gain with short axes and with float32, which the
+// convolution does not use.  The lines lie where the convolution was not slower
+// than the transforms, tuned ones too, on any grid of the kind (extents 8 to
+// 1024; 400 thousand to 30 million points x vectors), for modes near the origin
+// (at most 4 from it along every axis, random off the axes) and far from it (any).
+// us, convolution : transforms, at the line and past it:
+//   float64  near  32^4 (d = 2, n = 4), 29 vectors: 12 pairs 942 : 942
+//                  16^5 (d = 2, n = 5), 29 vectors: 4 pairs 536 : 709, 6 760 : 709
+//                  32^3 x 16 (d = 1, n = 4), 57 vectors: 12 pairs 756 : 917, 16 1221 : 917
+//                  16^3 x 16^2 (d = 3, n = 5), 29 vectors: 4 pairs 662 : 713, 6 740 : 713
+//            far   32^4: 4 pairs 677 : 942, 6 942 : 942, 8 1197 : 942
+//                  32^3 x 16: 4 pairs 612 : 917, 6 878 : 917, 8 1104 : 917
+//   float32  near  32^4: 4 pairs 477 : 501, 6 573 : 501
+//                  16^5: 2 pairs 397 : 466, 3 522 : 466
+//                  64^2 x 32 (d = 1, n = 3), 229 vectors: 8 pairs 405 : 606, 16 1071 : 606
+//                  64 x 1024 (d = 1, n = 2), 256 vectors: 12 pairs 294 : 451, 16 587 : 451
+//            far   32^4: 2 pairs 395 : 501, 3 533 : 501
+// Grids of at most 16,384 points are bound by latency up to 64 vectors, and take
+// more pairs (us, 64 vectors, convolution : AUTO's transforms):
+//   d = 1  n = 2, 4096 points: 16 pairs 18.6 : 26.5, float32 : 19.6
+//          n = 3, 8192: 12 pairs 20 : 35 (float32 : 24), 16 32 : 35 (: 24)
+//          n = 4, 8000: 8 pairs 18.5 : 25 (float32 : 22), 12 29 : 25
+//   d = 2  6400: 12 pairs 25 : 31, 8 17 : 27 (float32);  d = 3  6144: 6 pairs 14 : 27
+// (Of 256 vectors and more the longest lose there: 4096 points, d = 1, n = 2, 16
+// pairs 43 : 31.  The route is the plan's all the same, so that a vector's result
+// does not depend on the block it is in.)  On 644 random potentials, grids and
+// blocks of up to 64 vectors that take the convolution none was slower.
+// A lattice of cosines, one near pair an axis, reaches along one axis at a time
+// and always takes it (28 kinds of grid, the least gain 373 : 445 in float32 on
+// 8 x 16^4), a star above all (16^6, 3 vectors: 497 against 1,733 and 1,082).
+constexpr int kNearModes = 4, kSmallGrid = 16384;
+static int stencil_max_pairs(int d, int n, int N, int prec, bool near) {
+    if (N <= kSmallGrid) {
+        if (d == 1) return n == 2 ? 16 : (n == 3 ? 12 : 8);
+        return d == 2 ? (prec ? 8 : 12) : (prec ? 4 : 6);
+    }
+    // [precision][near][slow axes: 1, 2, 3, more][d]
+    static const int line[2][2][4][3] = {{{{16, 12, 6}, {12, 4, 3}, {4, 3, 4}, {3, 4, 3}},
+                                          {{16, 12, 6}, {12, 12, 4}, {12, 4, 4}, {4, 4, 4}}},
+                                         {{{12, 6, 3}, {4, 2, 2}, {2, 2, 2}, {2, 2, 2}},
+                                          {{12, 8, 4}, {8, 4, 2}, {4, 2, 2}, {2, 2, 2}}}};
+    return line[prec][near ? 1 : 0][std::min(n - d, 4) - 1][d - 1];
 }
 
 static void build_stencil(iwfpm_plan_s* p) {
@@ -471,6 +500,7 @@ static void build_stencil(iwfpm_plan_s* p) {
     sd = StencilDesc{};
     sd.real = 1;
     int np = 0;
+    bool near = true, lattice = true, on_axis[kMaxAxes] = {};
     const int nm = (int)p->vre.size();
     for (int i = 0; i < nm; ++i) {
         const int* m = &p->modes[(size_t)i * n];
@@ -495,10 +525,18 @@ static void build_stencil(iwfpm_plan_s* p) {
         sd.cr[np] = re;
         sd.ci[np] = im;
         if (im != 0.0) sd.real = 0;
+        int reach = 0, axis = 0;  // axes that the pair reaches along, the last of them
         for (int j = 0; j < n; ++j) {
-            const int ax = axis_of(d, n, j), E = g.ext[ax];
-            sd.off[np][ax] = (short)(((m[j] % E) + E) % E);
+            const int ax = axis_of(d, n, j), E = g.ext[ax], off = ((m[j] % E) + E) % E;
+            sd.off[np][ax] = (short)off;
+            near = near && std::min(off, E - off) <= kNearModes;
+            if (off) {
+                ++reach;
+                axis = ax;
+            }
         }
+        lattice = lattice && reach == 1 && !on_axis[axis];
+        on_axis[axis] = true;
         ++np;
     }
 #define IWFPM_CASE(c) if (sd.np == 0 && c >= np) sd.np = c;
@@ -514,7 +552,7 @@ static void build_stencil(iwfpm_plan_s* p) {
     sd.tile_row = std::max(1, g.stride[0] / kStencilThreads / 8);
     build_star(p);
     for (int prec = 0; prec < 2; ++prec)
-        p->few_modes[prec] = p->star.ok || np <= stencil_max_pairs(d, prec);
+        p->few_modes[prec] = p->star.ok || (lattice && near) || np <= stencil_max_pairs(d, n, g.N, prec, near);
 }
 
 static const size_t kLdsDefault = 64 * 1024;
