@@ -218,8 +218,9 @@ int iwfpm_eigenfunction(iwfpm_plan_t plan, const void* u, const double* origin, 
  * iwfpm_batch_create - B plans on one device, convolution precision
  *   IWFPM_PREC_*; use_graph != 0 captures the batch's launches (one persistent
  *   launch per pass walking a work table in device memory) into a hipGraph on
- *   the first apply and replays it afterwards.  The plans must outlive the
- *   batch and must not be used concurrently with it.
+ *   the first apply and replays it afterwards (a batch of few-mode plans alone
+ *   has so few launches that they are issued directly).  The plans must outlive
+ *   the batch and must not be used concurrently with it.
  * iwfpm_batch_apply - hpsi[i] = H~_i psi[i] for nvec[i] vectors of plan i
  *   (device pointers, same layout as iwfpm_apply; nvec[i] = 0 skips plan i).
  *   Asynchronous on `stream`; the work table is refreshed by a copy on the same

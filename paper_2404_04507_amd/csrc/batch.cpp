@@ -26,7 +26,9 @@ struct iwfpm_batch_s {
     int prec = 0;
     int device = 0;
     std::vector<iwfpm_plan_s*> plans;
-    DeviceBuf d_table;           // BatchHead followed by B BatchItems
+    DeviceBuf d_table;           // BatchHead, B BatchItems, B FewCalls, B + 1 starts per few-mode launch
+    DeviceBuf d_few;             // B FewItems
+    std::vector<FewItem> items;  // the same on the host
     unsigned char* h_table = nullptr;  // pinned staging
     size_t table_bytes = 0;
     hipEvent_t staged = nullptr;  // the last copy out of the staging buffer
@@ -37,7 +39,7 @@ struct iwfpm_batch_s {
     bool all_transforms = false;          // no plan takes the few-mode route
     bool transforms = false;              // some plan takes the transform passes
     std::vector<FewLaunch> few;           // few-mode plans: one launch per kind of kernel
-    size_t few_off = 0, start_off = 0;    // table offsets: B FewItems, then B + 1 starts per launch
+    size_t call_off = 0, start_off = 0;   // table offsets of the FewCalls and the starts
     hipGraphExec_t gexec = nullptr;
     hipStream_t gstream = nullptr;
     bool few_of(const iwfpm_plan_s* p) const { return !all_transforms && p->few_modes[prec]; }
@@ -45,11 +47,42 @@ struct iwfpm_batch_s {
 
 static size_t items_offset() { return (sizeof(BatchHead) + 255) / 256 * 256; }
 
+// Few-mode plans without a walk have a kernel for each number of pairs.  In a
+// batch of small ones the launches cost more than the work, so they share the
+// kernel that takes any number; its registers are those of the largest, which
+// large batches would pay for.  us, a launch each : one launch : transforms, with
+// 2 to 12 pairs (float64, one vector, then six):
+//   8 plans of some 600 points          48 : 19 : 32     48 : 19 : 34
+//   16 of 10,000 (160 thousand in all)  42 : 30 : 38     45 : 36 : 43
+//   64 of 10,000 (640 thousand)        101 : 86 : 93    101 : 88 : 109
+//   64 of 26,000 (1.7 million)         102 : 130 : 114  123 : 166 : 198
+constexpr long long kJointPoints = 786432;
+// A graph costs more than the few launches that a batch of few-mode plans has
+// (one launch, 8 plans 41 : 19 us, 64 plans 117 : 86; five launches 54 : 48)
+constexpr size_t kDirectLaunches = 5;
+static void join_point_kinds(std::vector<FewItem>& items) {
+    for (int d = 1; d <= kStencilMaxD; ++d) {
+        long long points = 0;
+        int first = 0;
+        bool several = false;
+        for (const FewItem& it : items) {
+            if (it.kind / 100 != d) continue;
+            points += it.g.N;
+            several = several || (first && it.kind != first);
+            first = it.kind;
+        }
+        if (!several || points > kJointPoints) continue;
+        for (FewItem& it : items)
+            if (it.kind / 100 == d) it.kind = few_joint_kind(d);
+    }
+}
+
 static hipError_t launch_few(iwfpm_batch_s* b, hipStream_t st) {
     const unsigned char* table = (const unsigned char*)b->d_table.ptr;
     for (size_t k = 0; k < b->few.size(); ++k) {
         const int* start = reinterpret_cast<const int*>(table + b->start_off) + k * (b->B + 1);
-        hipError_t e = launch_few_batch(b->few[k], reinterpret_cast<const FewItem*>(table + b->few_off), start, b->B, st);
+        hipError_t e = launch_few_batch(b->few[k], (const FewItem*)b->d_few.ptr,
+                                        reinterpret_cast<const FewCall*>(table + b->call_off), start, b->B, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -119,32 +152,44 @@ int iwfpm::batch_create(int B, const iwfpm_plan_t* plans, int precision, int use
     b->maxs = extent_class_of(maxe);
     b->lds = lds;
     b->use_graph = use_graph != 0;
-    std::vector<FewItem> items(B);
+    b->items.resize(B);
     for (int i = 0; i < B; ++i) {
         const iwfpm_plan_s* p = plans[i];
-        items[i].kind = -1;
+        FewItem& it = b->items[i];
+        std::memset(&it, 0, sizeof(it));
+        it.kind = -1;
         if (!b->few_of(p)) {
             b->transforms = true;
             continue;
         }
-        items[i].g = p->geom;
-        items[i].sd = p->stencil;
-        items[i].w = p->star;
-        const int kind = items[i].kind = few_kind(p->geom, p->stencil, p->star);
-        bool known = false;
-        for (const FewLaunch& l : b->few) known = known || l.kind == kind;
-        if (!known) b->few.push_back(FewLaunch{kind, 0, 0, 0});
+        it.g = p->geom;
+        it.t = p->tabs;
+        it.sd = p->stencil;
+        it.w = p->star;
+        it.kind = few_kind(it.g, it.sd, it.w);
     }
-    b->few_off = (items_offset() + (size_t)B * sizeof(BatchItem) + 255) / 256 * 256;
-    b->start_off = (b->few_off + (size_t)B * sizeof(FewItem) + 255) / 256 * 256;
+    join_point_kinds(b->items);
+    for (const FewItem& it : b->items) {
+        bool known = it.kind < 0;
+        for (const FewLaunch& l : b->few) known = known || l.kind == it.kind;
+        if (!known) b->few.push_back(FewLaunch{it.kind, 0, 0, 0});
+    }
+    b->call_off = (items_offset() + (size_t)B * sizeof(BatchItem) + 255) / 256 * 256;
+    b->start_off = (b->call_off + (size_t)B * sizeof(FewCall) + 255) / 256 * 256;
     b->table_bytes = b->start_off + b->few.size() * (B + 1) * sizeof(int);
     int rc = dev_alloc(b->d_table, b->table_bytes);
     if (rc == IWFPM_OK && hipHostMalloc((void**)&b->h_table, b->table_bytes) != hipSuccess) rc = IWFPM_ERR_ALLOC;
     if (rc == IWFPM_OK && hipEventCreateWithFlags(&b->staged, hipEventDisableTiming) != hipSuccess)
         rc = IWFPM_ERR_DEVICE;
+    if (rc == IWFPM_OK && !b->few.empty()) {
+        rc = dev_alloc(b->d_few, (size_t)B * sizeof(FewItem));
+        if (rc == IWFPM_OK &&
+            hipMemcpy(b->d_few.ptr, b->items.data(), (size_t)B * sizeof(FewItem), hipMemcpyHostToDevice) != hipSuccess)
+            rc = IWFPM_ERR_DEVICE;
+    }
     int per_cu = 0, cus = 0;
     for (FewLaunch& l : b->few)
-        if (rc == IWFPM_OK && few_launch_config(l, items.data(), B) != hipSuccess) rc = IWFPM_ERR_DEVICE;
+        if (rc == IWFPM_OK && few_launch_config(l, b->items.data(), B) != hipSuccess) rc = IWFPM_ERR_DEVICE;
     if (rc == IWFPM_OK && b->transforms) {
         hipError_t e = prec ? occupancy<float>(b->maxs, lds, &per_cu) : occupancy<double>(b->maxs, lds, &per_cu);
         if (e != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -182,26 +227,20 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
     BatchHead* head = reinterpret_cast<BatchHead*>(b->h_table);
     BatchItem* items = reinterpret_cast<BatchItem*>(b->h_table + items_offset());
     int tot[3] = {0, 0, 0};
-    FewItem* few = reinterpret_cast<FewItem*>(b->h_table + b->few_off);
+    FewCall* calls = reinterpret_cast<FewCall*>(b->h_table + b->call_off);
     int* start = reinterpret_cast<int*>(b->h_table + b->start_off);
     double few_points = 0.0;
     for (int i = 0; i < b->B; ++i)
-        if (b->few_of(b->plans[i])) few_points += (double)b->plans[i]->geom.N * nvec[i];
+        if (b->items[i].kind >= 0) few_points += (double)b->items[i].g.N * nvec[i];
     for (int i = 0; i < b->B; ++i) {
+        FewCall& c = calls[i];
+        std::memset(&c, 0, sizeof(c));
+        c.psi = reinterpret_cast<const double2*>(psi[i]);
+        c.hpsi = reinterpret_cast<double2*>(hpsi[i]);
+        c.nvec = nvec[i];
+    }
+    for (int i = 0; b->transforms && i < b->B; ++i) {
         iwfpm_plan_s* p = b->plans[i];
-        few[i].kind = -1;
-        if (b->few_of(p)) {
-            FewItem& f = few[i];
-            std::memset(&f, 0, sizeof(f));
-            f.g = p->geom;
-            f.t = p->tabs;
-            f.sd = p->stencil;
-            f.w = p->star;
-            f.psi = reinterpret_cast<const double2*>(psi[i]);
-            f.hpsi = reinterpret_cast<double2*>(hpsi[i]);
-            f.nvec = nvec[i];
-            f.kind = few_kind(f.g, f.sd, f.w);
-        }
         const Schedule& sc = p->sched[b->prec];
         BatchItem& it = items[i];
         std::memset(&it, 0, sizeof(it));
@@ -215,7 +254,7 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
         it.fused = sc.fused ? 1 : 0;
         for (int k = 0; k < 3; ++k) it.start[k] = tot[k];
         const int nv = nvec[i];
-        if (few[i].kind >= 0) {
+        if (b->items[i].kind >= 0) {
             // no workgroups here: see below
         } else if (sc.fused) {
             tot[0] += nv;
@@ -236,21 +275,23 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
         // plans of 24^2 x 32^2 points, one vector each: 93 -> 54 us)
         int rot = 0;
         for (int i = 0; i < b->B; ++i) {
-            FewItem& f = few[i];
             s[i + 1] = s[i];
-            if (f.kind != b->few[k].kind) continue;
-            s[i + 1] += few_blocks(f, few_points);
-            f.rot = (8 - rot) & 7;
-            rot = (rot + f.w.chunks * f.nvec) & 7;
+            if (b->items[i].kind != b->few[k].kind) continue;
+            FewCall& c = calls[i];
+            s[i + 1] += few_blocks(b->items[i], c, few_points);
+            c.rot = (8 - rot) & 7;
+            rot = (rot + c.w.chunks * c.nvec) & 7;
         }
     }
     head->B = b->B;
     for (int k = 0; k < 3; ++k) head->total[k] = tot[k];
-    if (hipMemcpyAsync(b->d_table.ptr, b->h_table, b->table_bytes, hipMemcpyHostToDevice, st) != hipSuccess)
+    const size_t from = b->transforms ? 0 : b->call_off;
+    if (hipMemcpyAsync((unsigned char*)b->d_table.ptr + from, b->h_table + from, b->table_bytes - from,
+                       hipMemcpyHostToDevice, st) != hipSuccess)
         return IWFPM_ERR_DEVICE;
     if (hipEventRecord(b->staged, st) != hipSuccess) return IWFPM_ERR_DEVICE;
     // graphs cannot be captured on the null stream: launch directly there
-    if (!b->use_graph || st == nullptr)
+    if (!b->use_graph || st == nullptr || (!b->transforms && b->few.size() <= kDirectLaunches))
         return (b->prec ? launch_passes<float>(b, st) : launch_passes<double>(b, st)) == hipSuccess ? IWFPM_OK
                                                                                                    : IWFPM_ERR_DEVICE;
     if (!b->gexec || b->gstream != st) {
@@ -281,6 +322,7 @@ int iwfpm_batch_destroy(iwfpm_batch_t b) {
         if (b->staged) (void)hipEventDestroy(b->staged);
         (void)hipDeviceSynchronize();
         dev_free(b->d_table);
+        dev_free(b->d_few);
         if (b->h_table) (void)hipHostFree(b->h_table);
     }
     delete b;

@@ -544,44 +544,60 @@ __device__ __forceinline__ int few_item(const int* __restrict__ start, int B, in
     return lo;
 }
 
-// Items are not written while a launch reads them, and as constant memory their
-// fields can stay in registers across a workgroup's stores.  As plain memory
-// they were read again after every store (a sweep of eight windows with 1 to 8
-// vectors 191 -> 181 us).
-__device__ __forceinline__ const FewItem& constant_item(const FewItem* items, int i) {
-    typedef const __attribute__((address_space(4))) FewItem* ConstantItems;
-    return *(const FewItem*)((ConstantItems)(unsigned long long)items + i);
+// Items and calls are not written while a launch reads them, and as constant
+// memory their fields can stay in registers across a workgroup's stores.  As
+// plain memory they were read again after every store (a sweep of eight windows
+// with 1 to 8 vectors 191 -> 181 us).
+template <typename T>
+__device__ __forceinline__ const T& constant_item(const T* items, int i) {
+    typedef const __attribute__((address_space(4))) T* ConstantItems;
+    return *(const T*)((ConstantItems)(unsigned long long)items + i);
 }
 
 template <int N, int D>
 __global__ void __launch_bounds__(star_threads(N)) k_batch_star(const FewItem* __restrict__ items,
+                                                                const FewCall* __restrict__ calls,
                                                                 const int* __restrict__ start, int B) {
     extern __shared__ __align__(16) unsigned char smem[];
     for (int w = blockIdx.x; w < start[B]; w += gridDim.x) {
         const int i = few_item(start, B, w);
         const FewItem& it = constant_item(items, i);
+        const FewCall& c = constant_item(calls, i);
         int tile, v, chunk;
         const int local = w - start[i];
-        if (!star_place(it.w, it.nvec, (local & ~7) | ((local + it.rot) & 7), tile, v, chunk)) continue;
+        if (!star_place(c.w, c.nvec, (local & ~7) | ((local + c.rot) & 7), tile, v, chunk)) continue;
         const long long off = (long long)v * it.g.N;
         __syncthreads();  // the previous item's LDS is no longer read
-        star_body<N, D, 1>(it.g, it.t, it.sd, it.w, it.psi + off, it.hpsi + off, tile, chunk * it.w.steps, smem);
+        star_body<N, D, 1>(it.g, it.t, it.sd, c.w, c.psi + off, c.hpsi + off, tile, chunk * c.w.steps, smem);
     }
 }
 
+// NP = 0: items of any number of pairs
 template <int D, int NP>
 __global__ void __launch_bounds__(kStencilThreads) k_batch_stencil(const FewItem* __restrict__ items,
+                                                                   const FewCall* __restrict__ calls,
                                                                    const int* __restrict__ start, int B) {
     extern __shared__ __align__(16) unsigned char smem[];
     for (int w = blockIdx.x; w < start[B]; w += gridDim.x) {
         const int i = few_item(start, B, w);
         const FewItem& it = constant_item(items, i);
-        const int local = w - start[i], vg = local / it.gx;
-        const int tile = stencil_tile(local - vg * it.gx, it.sd.tile_row);
+        const FewCall& c = constant_item(calls, i);
+        const int local = w - start[i], vg = local / c.gx;
+        const int tile = stencil_tile(local - vg * c.gx, it.sd.tile_row);
         if ((long long)tile * kStencilThreads >= it.g.N) continue;
+        const int v0 = vg * c.vb, v1 = min(c.nvec, v0 + c.vb);
+        int4* tab = reinterpret_cast<int4*>(smem);
         __syncthreads();
-        stencil_body<D, NP>(it.g, it.t, it.sd, it.psi, it.hpsi, tile, vg * it.vb, min(it.nvec, (vg + 1) * it.vb),
-                            reinterpret_cast<int4*>(smem));
+        if constexpr (NP > 0) {
+            stencil_body<D, NP>(it.g, it.t, it.sd, c.psi, c.hpsi, tile, v0, v1, tab);
+        } else {
+            switch (it.sd.np) {
+#define IWFPM_CASE(np_) \
+    case np_: stencil_body<D, np_>(it.g, it.t, it.sd, c.psi, c.hpsi, tile, v0, v1, tab); break;
+                IWFPM_STENCIL_PAIRS(IWFPM_CASE)
+#undef IWFPM_CASE
+            }
+        }
     }
 }
 
@@ -724,7 +740,12 @@ hipError_t launch_stencil(const DevGeom& g, const DevTabs& t, const StencilDesc&
         if (g.n == 4) return launch_star<4, 2>(g, t, sd, w, x, y, nvec, st);
         return launch_star<6, 3>(g, t, sd, w, x, y, nvec, st);
     }
-#define IWFPM_CASE(np_)                                                                 if (sd.np == np_) {                                                                     if (g.d == 1) return launch_points<1, np_>(g, t, sd, x, y, nvec, st);               if (g.d == 2) return launch_points<2, np_>(g, t, sd, x, y, nvec, st);               return launch_points<3, np_>(g, t, sd, x, y, nvec, st);                         }
+#define IWFPM_CASE(np_)                                                       \
+    if (sd.np == np_) {                                                       \
+        if (g.d == 1) return launch_points<1, np_>(g, t, sd, x, y, nvec, st); \
+        if (g.d == 2) return launch_points<2, np_>(g, t, sd, x, y, nvec, st); \
+        return launch_points<3, np_>(g, t, sd, x, y, nvec, st);               \
+    }
     IWFPM_STENCIL_PAIRS(IWFPM_CASE)
 #undef IWFPM_CASE
     return hipErrorInvalidValue;
@@ -738,19 +759,19 @@ int few_kind(const DevGeom& g, const StencilDesc& sd, const StarDesc& w) {
     return w.ok ? g.n : 100 * g.d + sd.np;
 }
 
-int few_blocks(FewItem& it, double total) {
-    if (it.nvec == 0) return 0;
+int few_blocks(const FewItem& it, FewCall& c, double total) {
+    if (c.nvec == 0) return 0;
     const DevGeom& g = it.g;
     if (it.w.ok) {
-        if (g.n == 2) it.w = star_config<2, 1, 1>(g, it.w, total);
-        else if (g.n == 3) it.w = star_config<3, 2, 1>(g, it.w, total);
-        else if (g.n == 4) it.w = star_config<4, 2, 1>(g, it.w, total);
-        else it.w = star_config<6, 3, 1>(g, it.w, total);
-        return star_blocks(it.w, it.nvec);
+        if (g.n == 2) c.w = star_config<2, 1, 1>(g, it.w, total);
+        else if (g.n == 3) c.w = star_config<3, 2, 1>(g, it.w, total);
+        else if (g.n == 4) c.w = star_config<4, 2, 1>(g, it.w, total);
+        else c.w = star_config<6, 3, 1>(g, it.w, total);
+        return star_blocks(c.w, c.nvec);
     }
-    it.vb = std::min(stencil_vb(g, total), it.nvec);
-    it.gx = stencil_gx(g, it.sd);
-    return it.gx * ((it.nvec + it.vb - 1) / it.vb);
+    c.vb = std::min(stencil_vb(g, total), c.nvec);
+    c.gx = stencil_gx(g, it.sd);
+    return c.gx * ((c.nvec + c.vb - 1) / c.vb);
 }
 
 // threads that the plan's star workgroups have, and the LDS of their rows on
@@ -776,6 +797,9 @@ static hipError_t with_batch_kernel(int kind, F&& f) {
         case 300 + np_: return f(k_batch_stencil<3, np_>);
         IWFPM_STENCIL_PAIRS(IWFPM_CASE)
 #undef IWFPM_CASE
+        case 1001: return f(k_batch_stencil<1, 0>);
+        case 1002: return f(k_batch_stencil<2, 0>);
+        case 1003: return f(k_batch_stencil<3, 0>);
         default: return hipErrorInvalidValue;
     }
 }
@@ -802,9 +826,10 @@ hipError_t few_launch_config(FewLaunch& l, const FewItem* items, int B) {
     });
 }
 
-hipError_t launch_few_batch(const FewLaunch& l, const FewItem* items, const int* start, int B, hipStream_t st) {
+hipError_t launch_few_batch(const FewLaunch& l, const FewItem* items, const FewCall* calls, const int* start, int B,
+                            hipStream_t st) {
     return with_batch_kernel(l.kind, [&](auto* k) {
-        k<<<dim3(l.grid), l.threads, l.lds, st>>>(items, start, B);
+        k<<<dim3(l.grid), l.threads, l.lds, st>>>(items, calls, start, B);
         return hipGetLastError();
     });
 }

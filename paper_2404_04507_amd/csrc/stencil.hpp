@@ -76,17 +76,20 @@ hipError_t launch_stencil(const DevGeom& g, const DevTabs& t, const StencilDesc&
                           const void* psi, void* hpsi, int nvec, hipStream_t st);
 hipError_t prepare_stencil();
 
-// Ragged batches: one launch per kind of kernel (few_kind) over the batch's
-// items of that kind.
+// Ragged batches: one launch per kind of kernel over the batch's items of that
+// kind.  What a plan has is uploaded once, what a call brings with each apply.
 struct FewItem {
     DevGeom g;
     DevTabs t;
     StencilDesc sd;
     StarDesc w;
+    int kind;        // few_kind or few_joint_kind, -1: not a few-mode plan
+};
+struct FewCall {
+    StarDesc w;      // star: the item's, with this call's walk
     const double2* psi;
     double2* hpsi;
     int nvec;
-    int kind;        // few_kind, -1: not a few-mode plan
     int rot;         // star: XCDs that its groups of workgroups are turned by
     int gx, vb;      // point kernel: workgroups per group of vectors, vectors of a group
 };
@@ -95,11 +98,14 @@ struct FewLaunch {
     size_t lds;
 };
 int few_kind(const DevGeom& g, const StencilDesc& sd, const StarDesc& w);
-// sets the item's walk for a launch of `total` points; its workgroups (a multiple of 8)
-int few_blocks(FewItem& it, double total);
+// the kind of the point kernel that takes any number of pairs
+inline int few_joint_kind(int d) { return 1000 + d; }
+// sets the call's walk for a launch of `total` points; its workgroups (a multiple of 8)
+int few_blocks(const FewItem& it, FewCall& call, double total);
 // threads, LDS and grid of the launch of l.kind, for any counts of vectors
 hipError_t few_launch_config(FewLaunch& l, const FewItem* items, int B);
 // start: first workgroup of each item (items of another kind have none), start[B] the total
-hipError_t launch_few_batch(const FewLaunch& l, const FewItem* items, const int* start, int B, hipStream_t st);
+hipError_t launch_few_batch(const FewLaunch& l, const FewItem* items, const FewCall* calls, const int* start, int B,
+                            hipStream_t st);
 
 }  // namespace iwfpm
