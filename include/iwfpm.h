@@ -249,8 +249,8 @@ int iwfpm_batch_destroy(iwfpm_batch_t batch);
  * extents) are reused and new ones appended (one line per key).  best_us
  * (may be NULL) receives the best time per apply in microseconds, or -1 when
  * the cache answered.  Allocates 2 x nvec vectors of scratch; blocking.
- * Where the plan's applies take the few-mode convolution, this is the schedule
- * of its solves.
+ * Where the plan's applies take the few-mode convolution, the schedule is that
+ * of its solves, and best_us the time of the convolution.
  * iwfpm_schedule - the current transform schedule for `precision` (also where
  * the few-mode convolution is taken instead): out[5] = {fused,
  * split, tile, slabs per workgroup, threads of the middle pass's workgroups
