@@ -230,14 +230,24 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
     FewCall* calls = reinterpret_cast<FewCall*>(b->h_table + b->call_off);
     int* start = reinterpret_cast<int*>(b->h_table + b->start_off);
     double few_points = 0.0;
-    for (int i = 0; i < b->B; ++i)
-        if (b->items[i].kind >= 0) few_points += (double)b->items[i].g.N * nvec[i];
     for (int i = 0; i < b->B; ++i) {
         FewCall& c = calls[i];
         std::memset(&c, 0, sizeof(c));
+        if (b->items[i].kind < 0 || nvec[i] == 0) continue;
+        // results over the vectors themselves: the convolution reads neighbours,
+        // while the transforms have read all of a vector before they write it
+        const char *x = (const char*)psi[i], *y = (const char*)hpsi[i];
+        const size_t bytes = (size_t)nvec[i] * (size_t)b->items[i].g.N * 16;
+        if (x < y + bytes && y < x + bytes) {
+            const int rc = plan_apply(b->plans[i], psi[i], hpsi[i], nvec[i],
+                                      b->prec ? IWFPM_PREC_FP32 : IWFPM_PREC_FP64, st, 1, true);
+            if (rc) return rc;
+            continue;
+        }
         c.psi = reinterpret_cast<const double2*>(psi[i]);
         c.hpsi = reinterpret_cast<double2*>(hpsi[i]);
         c.nvec = nvec[i];
+        few_points += (double)b->items[i].g.N * nvec[i];
     }
     for (int i = 0; b->transforms && i < b->B; ++i) {
         iwfpm_plan_s* p = b->plans[i];
