@@ -281,8 +281,9 @@ int iwfpm_batch_apply(iwfpm_batch_t b, const void* const* psi, void* const* hpsi
         s[0] = 0;
         // A star item deals its groups (the steps of one vector) to the XCDs from
         // the first on, and the next item goes on where it ended: all from the
-        // first left the last XCDs idle (eight windows, ragged: 181 -> 146 us; 8
-        // plans of 24^2 x 32^2 points, one vector each: 93 -> 54 us)
+        // first left the last XCDs idle (the launch on eight windows, ragged, 181
+        // -> 146 us of the call's 224 -> 178; 8 plans of 24^2 x 32^2 points, one
+        // vector each: 93 -> 54 us)
         int rot = 0;
         for (int i = 0; i < b->B; ++i) {
             s[i + 1] = s[i];

@@ -42,19 +42,18 @@ __device__ __forceinline__ double gelu_grad(double x) {
 }
 
 // ---------------------------------------------------------------------------
-// dense layers of the shell MLP on the matrix cores (v_mfma_f32_16x16x16_bf16,
-// float32 accumulation).  The weights are bfloat16; an operand held in
-// float32 (activations, gradients) is split into three bfloat16 terms
-// x = h + m + l (each the round-to-nearest of what the previous ones left),
-// which carry its full 24-bit significand, and products of bfloat16 terms are
-// exact in float32, so each layer computes what a float32 loop over the
-// bf16-rounded weights would, up to the order of the float32 additions.
+// dense layers of the shell MLP on the matrix cores, weights in bfloat16.
 //
 // These products are small (1,024 shells x 256 x 256) and bound by latency: a
 // wave that walks K 16 values at a time, element by element, waits for its
 // loads again and again (94 us a product).
 //
-// Forward (k_mlp_fwd): one wave per 16 x 16 tile adds up K in steps of 16
+// Forward (k_mlp_fwd): float32 accumulation.  The float32 activations are split
+// into three bfloat16 terms x = h + m + l (each the round-to-nearest of what the
+// previous ones left), which carry the full 24-bit significand, and products of
+// bfloat16 terms are exact in float32, so a layer computes what a float32 loop
+// over the bf16-rounded weights would, up to the order of the float32 additions.
+// One wave per 16 x 16 tile adds up K in steps of 16
 // (v_mfma_f32_16x16x16_bf16: lane l holds A[l%16][4(l/16) .. 4(l/16)+3] and
 // B[4(l/16) .. 4(l/16)+3][l%16] and ends with D[4(l/16) + v][l%16], v < 4).
 // That order stays as it is: the outputs scale float64 directions, and these

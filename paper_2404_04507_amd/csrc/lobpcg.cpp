@@ -2063,7 +2063,8 @@ static int lobpcg(int B, iwfpm_plan_s* const* plans, const iwfpm_eigs_opts& o, c
     }
     auto V = [&](BInst& b, int buf, int v0, int cnt) { return Rt::vecs(b.c, buf, v0, cnt); };
     // H applied to the first cnt[i] trial vectors of bin into bout, by precision.
-    // Always by the transforms: a solve stops when its residuals pass, and where
+    // Always by the transforms (and so the learned preconditioner's convolutions):
+    // a solve stops when its residuals pass, and where
     // the wanted pairs end inside a cluster the values it stops at move by up to
     // (tol ||H||)^2 / gap with any change of the applies' rounding (1e-6 of the
     // eigenvalues seen at tol = 1e-8 on 24^2 x 32^2 points, lambda = 2).

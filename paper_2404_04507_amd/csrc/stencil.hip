@@ -9,9 +9,9 @@
 // most of them from registers and LDS.  Measured per apply, inputs rotating
 // through three sets (a 2 GiB device copy reaches 4.9 TB/s on the same card):
 //   24^2 x 32^2 points, 16 vectors: transforms 181 us (float32) and 332 us
-//     (float64), point kernel 96 us, star kernel 70 us, floor 60 us
+//     (float64), point kernel 96 us, star kernel 78 us, floor 60 us
 //   16^6, 8 vectors: transforms 3.13 ms (float32), point kernel 1.90 ms, star
-//     kernel 1.21 ms, floor 0.87 ms
+//     kernel 1.20 ms, floor 0.87 ms
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
